@@ -165,7 +165,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmParams p) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) v[r] = act_apply(v[r] + E::get4(rv, r), p.act2);
                 }
-                *(h4 *)((_Float16 *)p.y + off) = E::pack4(v);
+                if (p.yf) store_nhwc4<E>(p, v, m, nbase);
+                if (p.y) *(h4 *)((_Float16 *)p.y + off) = E::pack4(v);
             }
         }
     }

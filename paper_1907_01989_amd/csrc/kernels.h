@@ -35,7 +35,9 @@ struct GemmParams {
     const h8 *w;         // packed weights [nb16][ksp][16][8]
     const float *bias;   // [nb16 * 16]
     const h8 *res;       // sliced residual with the output's shape, or null
-    void *y;             // sliced fp16 output, or fp32 (M x cout) for FC
+    void *y;             // sliced fp16 output, or fp32 (M x cout) for FC; null: yf alone is written
+    float *yf;           // the output widened to an NHWC fp32 array (M x cout) as well, or null
+    int yvec;            // ... whose 4-channel groups start on 16 bytes
     int M;               // output pixels (n * oh * ow)
     int Min;             // input pixels (n * h * w)
     int ksl, ksp;        // K slices, and padded to a multiple of 4

@@ -1419,6 +1419,29 @@ void pack_weights(const mgi_graph &g, mgi_plan &p, const mgi_options &o) {
     p.weight_bytes = std::max<size_t>(blob.size(), 256);
 }
 
+// An fp32 graph output whose sliced tensor a GEMM node produces is written by
+// that node's kernel (the export node stays in the list and launches nothing).
+// Not with materialize_all, where every sliced tensor is kept to be read.
+void absorb_exports(mgi_plan &p) {
+    std::vector<int> readers(p.bufs.size(), 0), producer(p.bufs.size(), -1);
+    for (size_t i = 0; i < p.nodes.size(); ++i) {
+        const Node &nd = p.nodes[i];
+        for (int b : nd.in) readers[b]++;
+        if (nd.residual >= 0) readers[nd.residual]++;
+        producer[nd.out] = (int)i;
+    }
+    for (Node &ex : p.nodes) {
+        if (ex.kind != NodeKind::Export || p.bufs[ex.out].loc != Loc::Output) continue;
+        const int b = ex.in[0];
+        if (producer[b] < 0) continue;
+        Node &gm = p.nodes[producer[b]];
+        if (gm.kind != NodeKind::Gemm || gm.direct_out >= 0) continue;
+        gm.direct_out = ex.out;
+        gm.sliced_read = readers[b] > 1;
+        ex.absorbed = true;
+    }
+}
+
 mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p) {
     if (g.outputs.empty()) return fail(MGI_ERR_STATE, "mgi_graph_finalize: no output marked");
     mgi_status st = check_options(o);
@@ -1438,6 +1461,7 @@ mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p
     if (o.fuse && o.fuse_pool) fuse_pool_into_pw(p, o.fuse_pool == 2);
     if (o.fuse && o.fuse_softmax) fuse_softmax_into_fc(p);
     if (o.fuse && o.fuse_dwpw) fuse_dw_into_pw(p);
+    if (o.fuse && !o.materialize_all) absorb_exports(p);
     for (Node &nd : p.nodes) add_configs(p, nd, p.bufs[nd.out].shape.pixels());
     compute_lifetimes(p);
     plan_memory(p, o);

@@ -118,6 +118,13 @@ struct Node {
     std::vector<int> in;    // buffer ids
     int out = -1;           // buffer id
     int residual = -1;      // buffer id (Gemm / Stem epilogue), -1 = none
+    // Gemm: the fp32 graph output (buffer id) of the Export node that this
+    // node's kernel writes itself, -1 = none; whether anything else reads the
+    // sliced output (no: it is not stored).  Export: absorbed that way (its
+    // own kernel runs only where a run's buffers overlap, see run_plan)
+    int direct_out = -1;
+    bool sliced_read = true;
+    bool absorbed = false;
     int act1 = MGI_ACT_NONE, act2 = MGI_ACT_NONE;
     // weights in the packed blob
     size_t w_off = 0, w_bytes = 0, b_off = 0, b_bytes = 0;

@@ -31,7 +31,20 @@ struct Bases {
     char *ws;
     const void *const *ins;
     void *const *outs;
+    bool direct = false;   // graph outputs may be written before the last read of the graph inputs
 };
+
+// Whether no output buffer of a run shares bytes with an input buffer (a
+// caller may run in place: its inputs are then read before any output is
+// written, as when every output has an export kernel at the end).
+bool io_disjoint(const mgi_plan &p, const void *const *ins, void *const *outs) {
+    for (size_t i = 0; i < p.input_bufs.size(); ++i)
+        for (size_t o = 0; o < p.output_bufs.size(); ++o) {
+            const char *a = static_cast<const char *>(ins[i]), *b = static_cast<const char *>(outs[o]);
+            if (a < b + p.bufs[p.output_bufs[o]].bytes && b < a + p.bufs[p.input_bufs[i]].bytes) return false;
+        }
+    return true;
+}
 
 void *buf_ptr(const mgi_plan &p, int b, const Bases &B) {
     const Buf &f = p.bufs[b];
@@ -373,6 +386,16 @@ hipError_t launch_dwpw_node(const mgi_plan &p, const Node &nd, const Bases &B, v
     return launch_dwpw(q, t, st);
 }
 
+// A node that launches nothing in this run: a timed run's events are still
+// recorded.
+hipError_t mark_events(hipStream_t st) {
+    const LaunchEvents &ev = launch_events();
+    hipError_t e = hipSuccess;
+    if (ev.start) e = hipEventRecord(ev.start, st);
+    if (ev.stop && e == hipSuccess) e = hipEventRecord(ev.stop, st);
+    return e;
+}
+
 hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStream_t st) {
     const char *wbase = static_cast<const char *>(p.dev_w);
     const Buf &ob = p.bufs[nd.out];
@@ -416,6 +439,11 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
             q.bias = (const float *)(wbase + nd.b_off);
             q.res = nd.residual >= 0 ? (const h8 *)buf_ptr(p, nd.residual, B) : nullptr;
             q.y = y;
+            if (B.direct && nd.direct_out >= 0) {
+                q.yf = (float *)buf_ptr(p, nd.direct_out, B);
+                q.yvec = os.c % 4 == 0 && ((uintptr_t)q.yf & 15) == 0;
+                if (!nd.sliced_read) q.y = nullptr;
+            }
             q.M = (int)os.pixels();
             q.Min = (int)ib.shape.pixels();
             q.ksl = nd.ksl; q.ksp = nd.ksp;
@@ -513,6 +541,7 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
                                  (int)ib.shape.pixels(), slices(ib.shape.c), ib.shape.c, bf, st);
         }
         case NodeKind::Export: {
+            if (nd.absorbed && B.direct) return mark_events(st);
             const Buf &ib = p.bufs[nd.in[0]];
             return launch_export((const h8 *)buf_ptr(p, nd.in[0], B), (float *)y,
                                  (int)ib.shape.pixels(), ib.shape.c, bf, st);
@@ -594,7 +623,7 @@ mgi_status run_plan(mgi_plan *p, const void *const *dev_inputs, void *const *dev
         if (!dev_outputs[i]) return fail(MGI_ERR_INVALID_ARG, std::string(who) + ": null output pointer");
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!ws) ws = static_cast<char *>(p->dev_ws);
-    Bases B{ws, dev_inputs, dev_outputs};
+    Bases B{ws, dev_inputs, dev_outputs, io_disjoint(*p, dev_inputs, dev_outputs)};
     LaunchEvents &ev = launch_events();
     for (size_t i = 0; i < p->nodes.size(); ++i) {
         ev.start = start_ev ? static_cast<hipEvent_t>(start_ev[i]) : nullptr;
@@ -775,7 +804,7 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
         destroy();
         return hip_fail(e, "mgi_plan_autotune: events");
     }
-    Bases B{static_cast<char *>(p->dev_ws), dev_inputs, dev_outputs};
+    Bases B{static_cast<char *>(p->dev_ws), dev_inputs, dev_outputs, io_disjoint(*p, dev_inputs, dev_outputs)};
     LaunchEvents &ev = launch_events();
     mgi_status result = MGI_OK;
     std::vector<float> times;

@@ -41,3 +41,78 @@ def test_ingest_export(n, h, w, c, src, dtype):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(yo.cpu().numpy().reshape(-1), want.cpu().numpy().reshape(-1))
         assert bool((yb[off + x.numel():] == 7.0).all()) and bool((yb[:off] == 7.0).all())
+
+
+DIRECT_CASES = [
+    # n, h, w, cin, cout, window, residual
+    (1, 1, 1, 8, 5, 1, False),
+    (3, 9, 7, 40, 21, 1, False),            # channel tail of a 4-channel group, ragged tiles
+    (2, 13, 13, 64, 136, 1, True),          # half a channel block at the end, residual
+    (5, 14, 14, 96, 64, 1, True),
+    (1, 33, 33, 24, 30, 3, False),          # implicit GEMM
+    (2, 9, 9, 16, 72, 3, True),
+]
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,k,res", DIRECT_CASES)
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_gemm_writes_nhwc_output(n, h, w, cin, cout, k, res, dtype):
+    """The GEMM kernels' own NHWC fp32 store, in every configuration, against
+    the sliced store and the export kernel (a plan that keeps every tensor),
+    with and without another reader of the sliced tensor; and a run whose
+    output buffer is its input buffer."""
+    import torch
+    from paper_1907_01989_amd import engine, _binding as B
+
+    def net(second):
+        g = NetBuilder(seed=cin + cout)
+        x = g.input(n, h, w, cin, -1, 1, dtype=workloads.DTYPE_FP32)
+        y = g.conv(x, cout, k, act=ACT_NONE)
+        if res:
+            y = g.add(y, g.activation(g.conv(x, cout, 1, act=ACT_NONE), workloads.ACT_RELU), act=ACT_NONE)
+        g.mark_output(y)
+        if second:
+            g.mark_output(g.gap(y))
+        return g.graph("direct")
+
+    for second in (False, True):
+        desc = net(second)
+        ref_plan = engine.Plan(desc, dtype=dtype, materialize_all=True)
+        x = ref_plan.input_tensors()
+        ref = ref_plan.run(x)
+        plan = engine.Plan(desc, dtype=dtype)
+        for i, (kind, (_, ncfg, _)) in enumerate(zip([m["kind"] for m in plan.nodes()], plan.node_configs())):
+            if kind not in ("pw_gemm", "conv_igemm"):
+                continue
+            for c in range(ncfg):
+                B.mgi_plan_set_node_config(plan.handle, i, c)
+                log(f"[case] direct {n}x{h}x{w}x{cin}->{cout} k{k} res{int(res)} dtype {dtype} "
+                    f"{kind} {plan.node_configs()[i][2]} readers {1 + int(second)}")
+                outs = [torch.full_like(o, 9.0) for o in ref]
+                plan.run(x, outs)
+                torch.cuda.synchronize()
+                for o, r in zip(outs, ref):
+                    np.testing.assert_array_equal(o.cpu().numpy(), r.cpu().numpy())
+            B.mgi_plan_set_node_config(plan.handle, i, 0)
+
+
+def test_output_in_the_input_buffer():
+    """Input and output may share memory, whole or in part: every input value
+    is read before an output value is written."""
+    import torch
+    from paper_1907_01989_amd import engine
+    g = NetBuilder(seed=4)
+    x = g.input(2, 17, 19, 48, -1, 1, dtype=workloads.DTYPE_FP32)
+    g.mark_output(g.conv(g.dw(x, 3), 48))
+    plan = engine.Plan(g.graph("inplace"))
+    xs = plan.input_tensors()
+    want = plan.run(xs)[0].cpu().numpy()
+    for shift in (0, 64):
+        log(f"[case] output buffer {shift} values into the input buffer")
+        buf = torch.empty(xs[0].numel() + shift, dtype=torch.float32, device="cuda")
+        xi = buf[:xs[0].numel()].view(xs[0].shape)
+        xi.copy_(xs[0])
+        yo = buf[shift:].view(xs[0].shape)
+        plan.run([xi], [yo])
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(yo.cpu().numpy(), want)
