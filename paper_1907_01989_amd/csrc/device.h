@@ -191,7 +191,15 @@ struct BF16 {
 // loads are ordered by explicit s_waitcnt + s_barrier instead.
 __device__ __forceinline__ void load_lds16(const h8 *src, const h8 *lds) {
     const unsigned la = (unsigned)(size_t)(__attribute__((address_space(3))) const void *)lds;
-    asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(la) : "memory");
+    // (s_nop: a write of m0 needs one wait state before a load to LDS reads it)
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(la) : "memory");
+}
+
+// the same from a wave-uniform base plus a 32-bit byte offset per lane: in a
+// loop the base advances by scalar instructions and the offsets stay
+__device__ __forceinline__ void load_lds16(const h8 *base, uint32_t off, const h8 *lds) {
+    const unsigned la = (unsigned)(size_t)(__attribute__((address_space(3))) const void *)lds;
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(la) : "memory");
 }
 
 // wait until at most N vector-memory instructions of this wave are in flight

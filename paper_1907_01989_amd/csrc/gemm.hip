@@ -287,7 +287,7 @@ __device__ __forceinline__ void pool_epilogue(const GemmParams &p, const f4 (&ac
 // BM pixels; an M-tile then holds p.ipt whole images and the epilogue writes
 // the pooled means (pool_epilogue), as in the pipelined kernel.
 template <typename E, int WM, int BN, int PF, bool POOL>
-__global__ __launch_bounds__(256) void gemm_xs_kernel(GemmParams p) {
+__global__ __launch_bounds__(256, 2) void gemm_xs_kernel(GemmParams p) {
     constexpr int FM = WM / 16, FN = BN / 16, BM = 4 * WM;
     extern __shared__ h8 wsm[];                  // [FN][ksp][16]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -425,24 +425,19 @@ hipError_t launch_gemm_xs(const GemmParams &p, int wm, int bn, int pf, bool pool
 #define MGI_XS_CASE(WM_, BN_, PF_) \
     if (wm == WM_ && bn == BN_ && pf == PF_) \
         return p.bf16 ? launch_xs<BF16, WM_, BN_, PF_, false>(p, st) : launch_xs<F16, WM_, BN_, PF_, false>(p, st);
-#define MGI_XS_PF(WM_, BN_) MGI_XS_CASE(WM_, BN_, 1) MGI_XS_CASE(WM_, BN_, 2) MGI_XS_CASE(WM_, BN_, 4) \
-    MGI_XS_CASE(WM_, BN_, 8)
+#define MGI_XS_PF(WM_, BN_) MGI_XS_CASE(WM_, BN_, 1) MGI_XS_CASE(WM_, BN_, 2) MGI_XS_CASE(WM_, BN_, 8)
     MGI_XS_CASE(16, 16, 8)
     MGI_XS_PF(16, 32)
     MGI_XS_PF(16, 64)
-    MGI_XS_PF(16, 128)
     MGI_XS_PF(32, 32)
     MGI_XS_PF(32, 64)
-    MGI_XS_PF(32, 128)
-    MGI_XS_PF(64, 32)
-    MGI_XS_PF(64, 64)
 #undef MGI_XS_PF
 #undef MGI_XS_CASE
     return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------
-// Pointwise GEMM, pipelined variant for mid and long K.  Re-reading the
+// GEMM, pipelined variant for mid and long K.  Re-reading the
 // activations for every 32-channel output block (the weight-slab kernel) costs
 // more L2->CU traffic than the per-CU load path delivers once K and the number
 // of output channels grow; here a workgroup owns a BM-pixel x BN-channel tile
@@ -466,34 +461,143 @@ struct PipeTile {
     static_assert(XE % 256 == 0 && WE % 256 == 0, "tile must be a multiple of 64 both ways");
 };
 
-template <int BM, int BN, int KS>
-__device__ __forceinline__ void pipe_issue(const GemmParams &p, int kk, h8 *st, int m0, int nb0,
-                                           int wave, int lane) {
-    using T = PipeTile<BM, BN, KS>;
-    const int k0 = kk * T::KS;
-#pragma unroll
-    for (int i = 0; i < T::XL; ++i) {
-        const int q = wave * T::XL + i;                  // wave load within the stage
-        const int e0 = q * 64, sl = e0 / BM, px = e0 - sl * BM;
-        const int ks = min(k0 + sl, p.ksl - 1);          // K tail meets zero weights
-        const int m = min(m0 + px + lane, p.M - 1);      // rows past M are never stored
-        load_lds16(p.x + (size_t)ks * p.M + m, st + e0);
-    }
-#pragma unroll
-    for (int i = 0; i < T::WL; ++i) {
-        const int L = wave * T::WL + i;                  // (output block, K-step) of the stage
-        const int q = L / T::SUB, sub = L - q * T::SUB;
-        const int nb = min(nb0 + q, p.nb16 - 1);
-        load_lds16(p.w + ((size_t)nb * p.ksp + k0 + 4 * sub) * 16 + lane, st + T::XE + L * 64);
-    }
+// The ring's loads of one wave.  Every wave load has a wave-uniform base and
+// per-lane 32-bit offsets that stay the same from stage to stage, so a stage
+// costs a few scalar additions per load and one vector addition: with one
+// wave per SIMD (a grid of about one workgroup per compute unit) the loop's
+// own instruction issue counts, 44 instructions for a 64 x 64 stage of two
+// K-steps here against 66 with 64-bit lane addresses and per-load clamps.
+// (Past that, two workgroups of 64 x 64 tiles on a compute unit run at their
+// LDS traffic, 24 KiB per K-step for 64 cycles of MFMA per SIMD.)
+//
+// TAPS: the activation half of a stage is gathered through the window of a
+// convolution (implicit GEMM).  K runs over taps, then input slices, and a
+// wave load is 64 pixels of one K slice, so its tap is the same in all lanes.
+// A lane adds its pixel's window origin, computed once, and reads the zero
+// element where its bit mask of taps inside the input says so (or past the
+// last K slice).  TAPS == 2: the input slices are a multiple of a stage, so a
+// stage has one tap; its addresses are formed when the tap changes and only
+// advance in between.  TAPS == 1: any slices, two reciprocal products per
+// wave load.  (The kernel these replaced staged each K step through registers
+// one step ahead, with four vector divisions per element: 3x3 over
+// 4 x 33 x 33 x 256 -> 256, 5.1 GFLOP, 44.3 us against 14.5.)
+__device__ __forceinline__ int div_uniform(int x, unsigned inv) {   // x, d < 32768, inv = ceil(2^31 / d)
+    return (int)__umulhi((unsigned)x << 1, inv);
 }
+
+template <int BM, int BN, int KS, int TAPS>
+struct PipeLoader {
+    using T = PipeTile<BM, BN, KS>;
+    static constexpr int PB = BM / 64;                  // 64-pixel blocks of a tile
+    static constexpr int NS = T::XL / PB;               // K slices a wave loads per stage
+    static_assert(T::XL % PB == 0, "a wave's loads start at the tile's first pixels");
+    const GemmParams &p;
+    int wave;
+    const h8 *xb;                                       // tile's first row (or image), slice 0
+    uint32_t xoff[PB];                                  // lane's pixels, bytes from xb
+    const h8 *wb[T::WL];                                // weights of the wave's loads, stage 0
+    uint32_t woff;                                      // lane, plus the stage
+    // TAPS
+    uint32_t mask[PB];                                  // taps inside the input
+    uint64_t at[T::XL], step[PB];                       // TAPS == 2: addresses of the current tap
+
+    __device__ __forceinline__ PipeLoader(const GemmParams &p_, int m0, int nb0, int wave_, int lane)
+        : p(p_), wave(wave_) {
+#pragma unroll
+        for (int i = 0; i < T::WL; ++i) {
+            const int L = wave * T::WL + i;              // (output block, K-step) of the stage
+            const int q = L / T::SUB, sub = L - q * T::SUB;
+            wb[i] = p.w + ((size_t)min(nb0 + q, p.nb16 - 1) * p.ksp + 4 * sub) * 16;
+        }
+        woff = lane * 16;
+        if constexpr (TAPS == 0) {
+            xb = p.x + m0;
+#pragma unroll
+            for (int b = 0; b < PB; ++b)                 // rows past M are never stored
+                xoff[b] = (uint32_t)min(b * 64 + lane, p.M - 1 - m0) * 16u;
+        } else {
+            const int hw = p.OH * p.OW, n0 = m0 / hw;
+            // (offsets from the origin of the tile's first image's first
+            // window, which keeps them non-negative)
+            xb = p.x + (size_t)n0 * p.H * p.W - (p.pt * p.W + p.pl);
+#pragma unroll
+            for (int b = 0; b < PB; ++b) {
+                const int m = min(m0 + b * 64 + lane, p.M - 1), n = m / hw, r = m - n * hw;
+                const int oy = r / p.OW, ox = r - oy * p.OW;
+                const int iy = oy * p.sh - p.pt, ix = ox * p.sw - p.pl;
+                xoff[b] = (uint32_t)((((n - n0) * p.H + oy * p.sh) * p.W + ox * p.sw) * 16);
+                uint32_t mk = 0, bit = 1;
+                for (int ky = 0; ky < p.kh; ++ky)
+                    for (int kx = 0; kx < p.kw; ++kx, bit <<= 1) {
+                        const bool in = (unsigned)(iy + ky * p.dh) < (unsigned)p.H && (unsigned)(ix + kx * p.dw) < (unsigned)p.W;
+                        mk |= in ? bit : 0u;
+                    }
+                mask[b] = mk;
+            }
+        }
+    }
+
+    // address of the lane's pixel of block b under tap `tap`, K slice ks's
+    // input slice s (selects, not branches: an address computed under a lane
+    // condition becomes an exec-masked branch)
+    __device__ __forceinline__ uint64_t tap_addr(int b, int tap, int s, bool &in) const {
+        const int ky = div_uniform(tap, p.inv_kw), kx = tap - ky * p.kw;
+        const uint64_t base = (uint64_t)(xb + (size_t)s * p.Min + (ky * p.dh * p.W + kx * p.dw));
+        in = (mask[b] & (1u << tap)) != 0;
+        const uint64_t a = base + xoff[b], z = (uint64_t)p.zero;
+        return ((uint64_t)(in ? (uint32_t)(a >> 32) : (uint32_t)(z >> 32)) << 32) | (in ? (uint32_t)a : (uint32_t)z);
+    }
+
+    // Loads of stage kk into `st`; stages are issued in order.  last: kk is
+    // the last stage (whose K slices may run past the end).
+    __device__ __forceinline__ void issue(int kk, h8 *st, bool last) {
+        const int k0 = kk * KS + wave * NS;              // the wave's first K slice
+        if constexpr (TAPS == 0) {
+#pragma unroll
+            for (int i = 0; i < T::XL; ++i) {
+                const int ks = last ? min(k0 + i / PB, p.ksl - 1) : k0 + i / PB;   // K tail meets zero weights
+                load_lds16(xb + (size_t)ks * p.M, xoff[i % PB], st + (wave * T::XL + i) * 64);
+            }
+        } else if constexpr (TAPS == 2) {
+            // (sin is a multiple of KS: the stage's tap, and its first slice)
+            const int tap = div_uniform(kk * KS, p.inv_sin), s0 = kk * KS - tap * p.sin;
+            if (s0 == 0) {
+#pragma unroll
+                for (int i = 0; i < T::XL; ++i) {
+                    bool in;
+                    at[i] = tap_addr(i % PB, tap, wave * NS + i / PB, in);
+                    if (tap * p.sin >= p.ksl) at[i] = (uint64_t)p.zero, in = false;   // stages past the end
+                    if (i < PB) step[i] = in ? (uint64_t)KS * p.Min * 16u : 0u;
+                    // (slices past a tap that reads zero: the same zero element)
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < T::XL; ++i) {
+                load_lds16((const h8 *)at[i], st + (wave * T::XL + i) * 64);
+                at[i] += step[i % PB];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < T::XL; ++i) {
+                const int ks = k0 + i / PB;
+                const int tap = div_uniform(ks, p.inv_sin);
+                bool in;
+                uint64_t a = tap_addr(i % PB, tap, ks - tap * p.sin, in);   // (past the end: no bit of the mask)
+                load_lds16((const h8 *)a, st + (wave * T::XL + i) * 64);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < T::WL; ++i) load_lds16(wb[i], woff, st + T::XE + (wave * T::WL + i) * 64);
+        woff += KS * 256;
+    }
+};
 
 // POOL: the output feeds only a global average pool over planes of p.hw <=
 // BM pixels; an M-tile then holds p.ipt whole images (rows mt * ipt * hw
 // on), and the epilogue writes the pooled means instead of the tile (see
-// pool_epilogue).
-template <typename E, int BM, int BN, bool POOL, int KS = 4>
-__global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmParams p) {
+// pool_epilogue).  TAPS: a windowed convolution (PipeLoader).
+template <typename E, int BM, int BN, bool POOL, int KS = 4, int TAPS = 0>
+__global__ __launch_bounds__(256, 2) void gemm_pipe_kernel(GemmParams p) {
     using T = PipeTile<BM, BN, KS>;
     constexpr int WMP = BM / 2, WNC = BN / 2, FM = WMP / 16, FN = WNC / 16;
     static_assert(WMP * WNC * 4 <= (T::XE + T::WE) * 16, "epilogue tile must fit one stage");
@@ -509,6 +613,7 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmParams p) {
     const int m0 = POOL ? mt * p.ipt * p.hw : mt * BM, nb0 = nt * (BN / 16);
     const int nk = p.ksp / T::KS;
 
+    PipeLoader<BM, BN, KS, TAPS> ld(p, m0, nb0, wave, lane);
     f4 acc[FN][FM];
 #pragma unroll
     for (int i = 0; i < FN; ++i) {
@@ -516,41 +621,77 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmParams p) {
 #pragma unroll
         for (int j = 0; j < FM; ++j) acc[i][j] = b0;
     }
+    ld.issue(0, st0, nk == 1);
+    if (nk > 1) ld.issue(1, st1, nk == 2);
+    if (nk > 2) ld.issue(2, st2, nk == 3);
+    if (nk > 3) ld.issue(3, st3, nk == 4);
 
-    pipe_issue<BM, BN, KS>(p, 0, st0, m0, nb0, wave, lane);
-    if (nk > 1) pipe_issue<BM, BN, KS>(p, 1, st1, m0, nb0, wave, lane);
-    if (nk > 2) pipe_issue<BM, BN, KS>(p, 2, st2, m0, nb0, wave, lane);
-
-    auto body = [&](int kk, const h8 *cur, h8 *nxt) {
-        // stage kk has landed once at most min(2, nk-1-kk) newer stages are
-        // pending; this wave's reads of the previous slot have returned, so
-        // after the barrier no wave still reads the slot refilled below
-        const int newer = min(2, nk - 1 - kk);
-        if (newer >= 2) wait_vm_lds<2 * T::LPW>();
-        else if (newer == 1) wait_vm_lds<T::LPW>();
-        else wait_vm_lds<0>();
-        __builtin_amdgcn_s_barrier();
-        if (kk + 3 < nk) pipe_issue<BM, BN, KS>(p, kk + 3, nxt, m0, nb0, wave, lane);
+    struct Frags {
+        h8 a[T::SUB][FN], b[T::SUB][FM];
+    };
+    auto read = [&](const h8 *st, Frags &f) {
 #pragma unroll
-        for (int sub = 0; sub < T::SUB; ++sub) {      // MFMA K-steps of the stage, in K order
-            h8 a[FN], b[FM];
+        for (int sub = 0; sub < T::SUB; ++sub) {
 #pragma unroll
-            for (int i = 0; i < FN; ++i) a[i] = cur[T::XE + ((wn * FN + i) * T::SUB + sub) * 64 + lane];
+            for (int i = 0; i < FN; ++i) f.a[sub][i] = st[T::XE + ((wn * FN + i) * T::SUB + sub) * 64 + lane];
 #pragma unroll
             for (int j = 0; j < FM; ++j)
-                b[j] = cur[(4 * sub + (lane >> 4)) * BM + wm * WMP + j * 16 + (lane & 15)];
+                f.b[sub][j] = st[(4 * sub + (lane >> 4)) * BM + wm * WMP + j * 16 + (lane & 15)];
+        }
+    };
+    auto mma = [&](const Frags &f) {
+#pragma unroll
+        for (int sub = 0; sub < T::SUB; ++sub)        // MFMA K-steps of the stage, in K order
 #pragma unroll
             for (int i = 0; i < FN; ++i)
 #pragma unroll
                 for (int j = 0; j < FM; ++j)
-                    acc[i][j] = E::mma(a[i], b[j], acc[i][j]);
-        }
+                    acc[i][j] = E::mma(f.a[sub][i], f.b[sub][j], acc[i][j]);
     };
-    for (int kk = 0; kk < nk; kk += 4) {
-        body(kk, st0, st3);
-        if (kk + 1 < nk) body(kk + 1, st1, st0);
-        if (kk + 2 < nk) body(kk + 2, st2, st1);
-        if (kk + 3 < nk) body(kk + 3, st3, st2);
+    // One stage: its fragments are in `f`; the next stage's are read into `g`
+    // while its MFMAs run.  Before the barrier a wave waits for its loads of
+    // stage kk + 1 (those of the stages after it stay in flight) and for its
+    // reads of stage kk; after it, stage kk + 1 is whole and no wave still
+    // reads stage kk, whose slot is refilled.
+    auto body = [&](int kk, Frags &f, Frags &g, h8 *cur, const h8 *nxt) {
+        wait_vm_lds<2 * T::LPW>();
+        __builtin_amdgcn_s_barrier();
+        ld.issue(kk + 4, cur, false);
+        read(nxt, g);
+        mma(f);
+    };
+    // ... and near the end: fewer stages in flight, the last one's K tail
+    auto tail = [&](int kk, Frags &f, Frags &g, h8 *cur, const h8 *nxt) {
+        if (kk + 1 < nk) {
+            const int newer = min(2, nk - 2 - kk);
+            if (newer >= 2) wait_vm_lds<2 * T::LPW>();
+            else if (newer == 1) wait_vm_lds<T::LPW>();
+            else wait_vm_lds<0>();
+            __builtin_amdgcn_s_barrier();
+            if (kk + 4 < nk) ld.issue(kk + 4, cur, kk + 5 == nk);
+            read(nxt, g);
+        }
+        mma(f);
+    };
+    Frags f0, f1;
+    if (nk > 3) wait_vm_lds<3 * T::LPW>();
+    else if (nk == 3) wait_vm_lds<2 * T::LPW>();
+    else if (nk == 2) wait_vm_lds<T::LPW>();
+    else wait_vm_lds<0>();
+    __builtin_amdgcn_s_barrier();
+    read(st0, f0);
+    int kk = 0;
+    for (; kk + 8 < nk; kk += 4) {                    // stages kk + 4 .. kk + 7 exist and are not the last
+        body(kk, f0, f1, st0, st1);
+        body(kk + 1, f1, f0, st1, st2);
+        body(kk + 2, f0, f1, st2, st3);
+        body(kk + 3, f1, f0, st3, st0);
+    }
+    for (; kk < nk; kk += 4) {
+        tail(kk, f0, f1, st0, st1);
+        if (kk + 1 < nk) tail(kk + 1, f1, f0, st1, st2);
+        if (kk + 2 < nk) tail(kk + 2, f0, f1, st2, st3);
+        if (kk + 3 < nk) tail(kk + 3, f1, f0, st3, st0);
     }
 
     __syncthreads();
@@ -569,6 +710,45 @@ static hipError_t launch_pipe_t(const GemmParams &p, hipStream_t st) {
     q.ntiles = (p.nb16 * 16 + BN - 1) / BN;
     launch((gemm_pipe_kernel<E, BM, BN, false>), dim3(q.mtiles * q.ntiles), dim3(256), 0, st, q);
     return hipGetLastError();
+}
+
+static unsigned inv31(int d) { return (unsigned)((0x80000000ull + d - 1) / d); }
+
+bool conv_pipe_ok(int kh, int kw, int ksp, int H, int W, int OH, int OW) {
+    // 32-bit byte offsets over the images a 128-row tile touches, and its
+    // window origins
+    const uint64_t imgs = 128 / ((uint64_t)OH * OW) + 3;
+    return (int64_t)kh * kw <= kMaxTaps && ksp < 32768 && imgs * H * W < (1ull << 26);
+}
+
+template <typename E, int BM, int BN, int KS>
+static hipError_t launch_conv_t(const GemmParams &p, hipStream_t st) {
+    GemmParams q = p;
+    q.mtiles = (p.M + BM - 1) / BM;
+    q.ntiles = (p.nb16 * 16 + BN - 1) / BN;
+    q.inv_sin = inv31(p.sin);
+    q.inv_kw = inv31(p.kw);
+    const dim3 grid(q.mtiles * q.ntiles), block(256);
+    if (p.sin % KS == 0) launch((gemm_pipe_kernel<E, BM, BN, false, KS, 2>), grid, block, 0, st, q);
+    else launch((gemm_pipe_kernel<E, BM, BN, false, KS, 1>), grid, block, 0, st, q);
+    return hipGetLastError();
+}
+
+template <typename E>
+static hipError_t launch_conv_e(const GemmParams &p, int bm, int bn, int ks, hipStream_t st) {
+    if (bm == 64 && bn == 32 && ks == 8) return launch_conv_t<E, 64, 32, 8>(p, st);
+    if (bm == 128 && bn == 32 && ks == 8) return launch_conv_t<E, 128, 32, 8>(p, st);
+    if (bm == 64 && bn == 64 && ks == 4) return launch_conv_t<E, 64, 64, 4>(p, st);
+    if (bm == 64 && bn == 128 && ks == 4) return launch_conv_t<E, 64, 128, 4>(p, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_conv(const GemmParams &p, int bm, int bn, int ks, hipStream_t st) {
+    if (p.M <= 0) return hipSuccess;
+    if (!p.taps || !p.zero || p.sin < 1 || p.kh < 1 || p.kw < 1 || p.ksp % 8 != 0 || p.ksl != p.kh * p.kw * p.sin ||
+        !conv_pipe_ok(p.kh, p.kw, p.ksp, p.H, p.W, p.OH, p.OW))
+        return hipErrorInvalidValue;
+    return p.bf16 ? launch_conv_e<BF16>(p, bm, bn, ks, st) : launch_conv_e<F16>(p, bm, bn, ks, st);
 }
 
 template <typename E, int BM, int BN>

@@ -45,8 +45,11 @@ struct GemmParams {
     int act1, act2;
     int mtiles, ntiles;
     int bf16;            // storage type: 0 fp16, 1 bf16
-    // implicit-GEMM window geometry
-    int H, W, OH, OW, sin, kw, sh, sw, dh, dw, pt, pl;
+    // implicit-GEMM window geometry (taps: the input is read through a window)
+    int H, W, OH, OW, sin, kh, kw, sh, sw, dh, dw, pt, pl;
+    int taps;
+    const h8 *zero;      // one zeroed element (read for taps outside the input)
+    unsigned inv_sin, inv_kw;   // ceil(2^31 / sin), ceil(2^31 / kw) (set by the launcher)
     // pooled GEMM: pixels per image, images, images per M-tile (set by the launcher)
     int hw, nimg, ipt;
     // FC with the softmax of its rows (sm_y non-null): probabilities (M x cout)
@@ -72,6 +75,13 @@ hipError_t launch_gemm_pipe(const GemmParams &p, int bm, int bn, hipStream_t st)
 // MFMA K-steps; needs ksp % 8 == 0), plain or pooled (as launch_gemm_pool);
 // same accumulation order as the 4-slice stages
 hipError_t launch_gemm_pipe_k8(const GemmParams &p, bool pool, hipStream_t st);
+// the pipelined GEMM over a window (implicit GEMM), ks (4 or 8) K slices per
+// ring stage, ksp % ks == 0; (bm, bn, ks) in kConvTiles.  conv_pipe_ok: the
+// shapes it covers (windows of at most kMaxTaps taps, offsets in range).
+constexpr int kMaxTaps = 31;
+constexpr int kConvTiles[4][3] = {{64, 64, 4}, {64, 32, 8}, {128, 32, 8}, {64, 128, 4}};
+bool conv_pipe_ok(int kh, int kw, int ksp, int H, int W, int OH, int OW);
+hipError_t launch_gemm_conv(const GemmParams &p, int bm, int bn, int ks, hipStream_t st);
 // pointwise GEMM whose output feeds only a global average pool: M-tiles of
 // bm rows hold bm / hw whole images (hw <= 64 pixels each, M = nimg * hw),
 // and the pooled means are written, sliced [ns][nimg], bit-identical to the

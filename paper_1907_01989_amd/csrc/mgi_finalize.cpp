@@ -107,6 +107,28 @@ std::string tile_name(const GemmTile &t) {
 
 void pick_pipe_tile(GemmTile &t, size_t M, int npad);
 
+// Windowed convolution through the ring: 64 x 64 tiles, except where another
+// shape measured faster (3x3, us):
+//  - 64 x 32 for at most 32 channels (60 x 60 x 368 -> 24, batch 21: 42.2
+//    against 51.9), and where 64 x 64 tiles would leave half the compute units
+//    idle (33 x 33 x 256 -> 256: 72 tiles 11.8, 144 narrow ones 8.5; at 392
+//    tiles 7.5 against 10.3);
+//  - 64 x 128 for more than 128 channels once it gives 1.5 workgroups per
+//    compute unit (26 x 26 x 216 -> 400, batch 11: 468 tiles 23.6 against 26.2;
+//    7 x 7 x 256 -> 512, batch 64: 196 tiles 16.1 against 15.2).
+GemmTile pick_conv_tile(size_t M, int npad) {
+    GemmTile t;
+    t.pipe = true;
+    const size_t m64 = (M + 63) / 64, t64 = m64 * (size_t)((npad + 63) / 64), t128 = m64 * (size_t)((npad + 127) / 128);
+    if (npad <= 32 || t64 <= 128) {
+        t.bn = 32;
+        t.ks = 8;
+    } else if (npad > 128 && t128 >= 384) {
+        t.bn = 128;
+    }
+    return t;
+}
+
 // Candidate tiles of a pointwise or implicit-GEMM node: the finalize-time
 // tile first, then pipelined, two-K-step and weight-slab tiles that fit.
 void add_gemm_configs(Node &nd, size_t M) {
@@ -119,6 +141,17 @@ void add_gemm_configs(Node &nd, size_t M) {
     };
     push(nd.tile);
     const int npad = nd.nb16 * 16;
+    if (nd.taps && nd.tile.pipe) {
+        for (auto &ct : kern::kConvTiles) {
+            if ((ct[1] > 64 && npad <= 64)) continue;
+            GemmTile t;
+            t.pipe = true;
+            t.bm = ct[0];
+            t.bn = ct[1];
+            t.ks = ct[2];
+            push(t);
+        }
+    }
     if (!nd.taps) {
         const int pipes[4][2] = {{128, 128}, {128, 64}, {64, 128}, {64, 64}};
         for (auto &pb : pipes) {
@@ -161,6 +194,7 @@ void add_gemm_configs(Node &nd, size_t M) {
             }
         }
     }
+    if (nd.taps && nd.tile.pipe) return;     // (the staged kernel: 44 us where the ring takes 15)
     const int ldss[5][2] = {{128, 128}, {64, 128}, {32, 128}, {64, 64}, {128, 64}};
     for (auto &lb : ldss) {
         if (lb[1] > 64 && npad <= 64) continue;
@@ -995,11 +1029,16 @@ mgi_status Lowering::lower_conv(const Group &G, const GOp &op, const Shape &out_
                     d.pad_t == 0 && d.pad_b == 0 && d.pad_l == 0 && d.pad_r == 0);
         nd.kname = nd.taps ? "conv_igemm" : "pw_gemm";
         nd.ksl = d.kh * d.kw * slices(x.c);
-        nd.ksp = (nd.ksl + 3) / 4 * 4;
+        // (windows of more than one K step: whole pairs of steps, for the
+        // tiles with two K-steps per stage)
+        nd.ksp = nd.taps && nd.ksl > 4 ? (nd.ksl + 7) / 8 * 8 : (nd.ksl + 3) / 4 * 4;
     }
     nd.nb16 = (d.cout + 15) / 16;
     nd.tile = pick_tile(out_shape.pixels(), d.cout);
-    if (nd.kind == NodeKind::Gemm && !nd.taps && nd.ksl >= 8 && nd.nb16 * 16 >= 64) {
+    if (nd.kind == NodeKind::Gemm && nd.taps && nd.ksp % 8 == 0 &&
+        kern::conv_pipe_ok(d.kh, d.kw, nd.ksp, x.h, x.w, out_shape.h, out_shape.w)) {
+        nd.tile = pick_conv_tile(out_shape.pixels(), nd.nb16 * 16);
+    } else if (nd.kind == NodeKind::Gemm && !nd.taps && nd.ksl >= 8 && nd.nb16 * 16 >= 64) {
         pick_pipe_tile(nd.tile, out_shape.pixels(), nd.nb16 * 16);
     } else if (nd.kind == NodeKind::Gemm && !nd.taps) {
         // weight-slab kernel: 128 x 32 tiles, two K steps of

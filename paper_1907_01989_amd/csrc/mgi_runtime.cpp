@@ -450,11 +450,14 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
             q.nb16 = nd.nb16; q.ns = slices(os.c); q.cout = os.c;
             q.act1 = nd.act1; q.act2 = nd.act2;
             q.H = ib.shape.h; q.W = ib.shape.w; q.OH = os.h; q.OW = os.w;
-            q.sin = slices(ib.shape.c); q.kw = nd.conv.kw;
+            q.sin = slices(ib.shape.c); q.kh = nd.conv.kh; q.kw = nd.conv.kw;
             q.sh = nd.conv.stride_h; q.sw = nd.conv.stride_w;
             q.dh = nd.conv.dil_h; q.dw = nd.conv.dil_w;
             q.pt = nd.conv.pad_t; q.pl = nd.conv.pad_l;
+            q.taps = nd.taps;
+            q.zero = (const h8 *)(wbase + p.zero_off);
             if (nd.kind == NodeKind::FC) return launch_fc(q, nd.tile.wm, nd.tile.pf, st);
+            if (nd.tile.pipe && nd.taps) return launch_gemm_conv(q, nd.tile.bm, nd.tile.bn, nd.tile.ks, st);
             if (nd.tile.pipe && nd.tile.ks == 8) return launch_gemm_pipe_k8(q, false, st);
             if (nd.tile.pipe) return launch_gemm_pipe(q, nd.tile.bm, nd.tile.bn, st);
             if (nd.tile.slab) return launch_gemm_xs(q, nd.tile.wm, nd.tile.bn, nd.tile.pf, false, st);

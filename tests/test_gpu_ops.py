@@ -14,7 +14,8 @@ import oracle
 import workloads
 from workloads import ACT_NONE, ACT_RELU, ACT_RELU6, NetBuilder
 
-from gpu_util import check_isolated, check_layer, isolated_reference, labels_check, log, run_gpu
+from gpu_util import (ISO_RTOL, ISO_RTOL_BF16, check_isolated, check_layer, isolated_reference, labels_check, log,
+                      run_gpu)
 
 pytestmark = pytest.mark.gpu
 
@@ -289,3 +290,44 @@ def test_mcfp_arena_runs_agree_with_greedy(net, batch):
     assert plan_m.memory_report()[1] != plan_g.memory_report()[1]
     for a, b in zip(outs_m, outs_g):
         np.testing.assert_array_equal(a, b)
+
+
+CONV_RING_CASES = [
+    # n, h, w, cin, cout, k, s, d, pads, fuse-residual: every tile of the window GEMM's ring
+    (1, 33, 33, 64, 64, 3, 1, 1, None, False),       # one tap per stage
+    (2, 19, 17, 32, 72, 3, 2, 1, None, True),        # 4 slices: one tap per 4-slice stage, two per 8-slice stage
+    (3, 9, 9, 24, 136, 3, 1, 2, None, False),        # taps change inside a stage, dilation 2
+    (70, 3, 3, 8, 16, 3, 1, 1, None, False),         # one slice per tap, many images per tile
+    (1, 130, 3, 128, 40, 3, 1, 1, (1, 1, 0, 2), False),   # taps wholly outside for some columns
+    (1, 1, 1, 64, 32, 5, 1, 1, (2, 2, 2, 2), False),  # a single pixel, 24 of 25 taps outside
+    (1, 12, 12, 16, 24, 6, 1, 1, (2, 3, 2, 3), False),   # more taps than the ring's mask holds
+    (4, 16, 16, 40, 48, 1, 2, 1, (0, 0, 0, 0), False),   # strided 1x1
+]
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,k,s,d,pads,res", CONV_RING_CASES)
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_conv_window_every_configuration(n, h, w, cin, cout, k, s, d, pads, res, dtype):
+    from paper_1907_01989_amd import engine, _binding as B
+    g = NetBuilder(seed=k * 100 + cin + cout)
+    x = sliced(g, g.input(n, h, w, cin, -1, 1))
+    y = g.conv(x, cout, k, s, d, act=ACT_NONE if res else ACT_RELU6, pads=pads)
+    if res:
+        oh, ow, _ = g.hwc(y)
+        y = g.add(y, sliced(g, g.input(n, oh, ow, cout, -2, 2)), act=ACT_RELU)
+    g.mark_output(y)
+    desc = g.graph(f"ring_{n}x{h}x{w}x{cin}->{cout}_k{k}s{s}d{d}")
+    if dtype:
+        desc = workloads.as_bf16_graph(desc)
+    ref = oracle.run_graph(desc)[y]
+    plan = engine.Plan(desc, bind=False, dtype=dtype)
+    i = [m["kind"] for m in plan.nodes()].index("conv_igemm")
+    first = None
+    for c in range(plan.node_configs()[i][1]):
+        B.mgi_plan_set_node_config(plan.handle, i, c)
+        log(f"[case] {desc['name']} dtype {dtype} {plan.node_configs()[i][2]}")
+        _, outs, _ = run_gpu(desc, materialize_all=False, dtype=dtype, configs={i: c})
+        if first is None:
+            first = outs[0]
+            check_isolated("conv", first, ref.reshape(first.shape), rtol=ISO_RTOL_BF16 if dtype else ISO_RTOL)
+        np.testing.assert_array_equal(outs[0], first)
