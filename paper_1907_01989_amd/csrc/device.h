@@ -81,6 +81,7 @@ __device__ __forceinline__ float fma_mix_from(uint32_t a, uint32_t b, float c) {
 }
 
 typedef uint32_t u4x __attribute__((ext_vector_type(4)));
+typedef uint32_t u2x __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ u4x as_u4(h8 v) { return __builtin_bit_cast(u4x, v); }
 
@@ -138,6 +139,23 @@ struct F16 {
     __device__ static void fma8_from(float *acc, const float *c0, h8 w, h8 v) {
         kern::fma8_from(acc, c0, as_u4(w), as_u4(v));
     }
+    // ... and four channels
+    __device__ static void fma4(float *acc, h4 w, h4 v) {
+        const u2x a = __builtin_bit_cast(u2x, w), b = __builtin_bit_cast(u2x, v);
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            fma_mix<0>(acc[2 * d], a[d], b[d]);
+            fma_mix<1>(acc[2 * d + 1], a[d], b[d]);
+        }
+    }
+    __device__ static void fma4_from(float *acc, const float *c0, h4 w, h4 v) {
+        const u2x a = __builtin_bit_cast(u2x, w), b = __builtin_bit_cast(u2x, v);
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            acc[2 * d] = fma_mix_from<0>(a[d], b[d], c0[2 * d]);
+            acc[2 * d + 1] = fma_mix_from<1>(a[d], b[d], c0[2 * d + 1]);
+        }
+    }
     __device__ static float get4(h4 v, int i) { return (float)v[i]; }
     __device__ static h4 pack4(const float *v) {
         h4 o;
@@ -170,6 +188,14 @@ struct BF16 {
     __device__ static void fma8_from(float *acc, const float *c0, h8 w, h8 v) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = fmaf(get(w, i), get(v, i), c0[i]);
+    }
+    __device__ static void fma4(float *acc, h4 w, h4 v) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = fmaf(get4(w, i), get4(v, i), acc[i]);
+    }
+    __device__ static void fma4_from(float *acc, const float *c0, h4 w, h4 v) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = fmaf(get4(w, i), get4(v, i), c0[i]);
     }
     __device__ static float get4(h4 v, int i) {
         return __uint_as_float((uint32_t)__builtin_bit_cast(u16x4, v)[i] << 16);

@@ -199,9 +199,23 @@ struct DwParams {
     h8 *y;
     int N, H, W, S, OH, OW, KH, KW, sh, sw, dh, dw, pt, pl, act;
     int bf16;            // storage type: 0 fp16, 1 bf16
+    // the NHWC graph input read in place of x, or null (8 * S channels, 16-byte
+    // aligned; where depthwise_reads_nhwc): fp16 or fp32
+    const void *xin;
+    int xin_fp16;
+    int ls;              // log2 of the slices of a group (set by the launcher)
 };
 // rows: output rows per thread of the 3x3 kernel (1, 2, 4 or 8; 0 = default)
 hipError_t launch_depthwise(const DwParams &p, int rows, hipStream_t st);
+bool depthwise_reads_nhwc(int KH, int KW, int sh, int sw, int dh, int dw, int N, int S, int OH, int OW);
+// band of the 5x5 kernel: output rows, the input rows and columns they read,
+// bands per image, LDS bytes, reciprocals of its index divisors (whole band or
+// group, last one)
+struct DwTile {
+    int rb, nrb, wp, nbands;
+    size_t lds;
+    double inv_wp, inv_ow, inv_nsl[2], inv_nrb[2];
+};
 
 // Pointwise convolution fused with the depthwise 3x3 convolution (dilation 1,
 // stride 1 or 2) that consumes its output: a workgroup owns a channel tile and

@@ -1481,6 +1481,30 @@ void absorb_exports(mgi_plan &p) {
     }
 }
 
+// A graph input that only a depthwise node reads, in whole slices, is read by
+// that node's kernel (the ingest node stays in the list and launches nothing).
+// Not with materialize_all.
+void absorb_ingests(mgi_plan &p) {
+    std::vector<int> readers(p.bufs.size(), 0);
+    for (const Node &nd : p.nodes) {
+        for (int b : nd.in) readers[b]++;
+        if (nd.residual >= 0) readers[nd.residual]++;
+    }
+    for (Node &in : p.nodes) {
+        if (in.kind != NodeKind::Ingest || readers[in.out] != 1 || p.bufs[in.out].shape.c % 8 != 0) continue;
+        for (Node &dw : p.nodes) {
+            const mgi_conv_desc &c = dw.conv;
+            const Shape &os = p.bufs[dw.out].shape;
+            if (dw.kind != NodeKind::Depthwise || dw.in[0] != in.out ||
+                !kern::depthwise_reads_nhwc(c.kh, c.kw, c.stride_h, c.stride_w, c.dil_h, c.dil_w, os.n,
+                                            slices(os.c), os.h, os.w))
+                continue;
+            dw.direct_in = in.in[0];
+            in.absorbed = true;
+        }
+    }
+}
+
 mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p) {
     if (g.outputs.empty()) return fail(MGI_ERR_STATE, "mgi_graph_finalize: no output marked");
     mgi_status st = check_options(o);
@@ -1500,7 +1524,10 @@ mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p
     if (o.fuse && o.fuse_pool) fuse_pool_into_pw(p, o.fuse_pool == 2);
     if (o.fuse && o.fuse_softmax) fuse_softmax_into_fc(p);
     if (o.fuse && o.fuse_dwpw) fuse_dw_into_pw(p);
-    if (o.fuse && !o.materialize_all) absorb_exports(p);
+    if (o.fuse && !o.materialize_all) {
+        absorb_exports(p);
+        absorb_ingests(p);
+    }
     for (Node &nd : p.nodes) add_configs(p, nd, p.bufs[nd.out].shape.pixels());
     compute_lifetimes(p);
     plan_memory(p, o);

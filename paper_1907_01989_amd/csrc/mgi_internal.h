@@ -120,10 +120,13 @@ struct Node {
     int residual = -1;      // buffer id (Gemm / Stem epilogue), -1 = none
     // Gemm: the fp32 graph output (buffer id) of the Export node that this
     // node's kernel writes itself, -1 = none; whether anything else reads the
-    // sliced output (no: it is not stored).  Export: absorbed that way (its
-    // own kernel runs only where a run's buffers overlap, see run_plan)
+    // sliced output (no: it is not stored)
     int direct_out = -1;
     bool sliced_read = true;
+    // Depthwise: the graph input (buffer id) that this node's kernel reads
+    // itself, -1 = none
+    int direct_in = -1;
+    // Export and Ingest: absorbed by their neighbour that way
     bool absorbed = false;
     int act1 = MGI_ACT_NONE, act2 = MGI_ACT_NONE;
     // weights in the packed blob

@@ -31,7 +31,7 @@ struct Bases {
     char *ws;
     const void *const *ins;
     void *const *outs;
-    bool direct = false;   // graph outputs may be written before the last read of the graph inputs
+    bool direct = false;   // kernels may read graph inputs and write graph outputs in place
 };
 
 // Whether no output buffer of a run shares bytes with an input buffer (a
@@ -54,6 +54,15 @@ void *buf_ptr(const mgi_plan &p, int b, const Bases &B) {
         case Loc::Output: return B.outs[f.index];
     }
     return nullptr;
+}
+
+// The graph input `b` for a kernel that reads it in place in 16-byte pieces,
+// or null where this run has to convert it first (the buffers overlap, or the
+// caller's array is not aligned).
+const void *direct_input(const mgi_plan &p, int b, const Bases &B) {
+    if (b < 0 || !B.direct) return nullptr;
+    const void *x = buf_ptr(p, b, B);
+    return ((uintptr_t)x & 15) ? nullptr : x;
 }
 
 inline int slices(int c) { return (c + 7) / 8; }
@@ -404,6 +413,7 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
     const bool bf = p.opt.dtype == MGI_DTYPE_BF16;
     switch (nd.kind) {
         case NodeKind::Ingest: {
+            if (nd.absorbed && direct_input(p, nd.in[0], B)) return mark_events(st);
             const Buf &ib = p.bufs[nd.in[0]];
             return launch_ingest(buf_ptr(p, nd.in[0], B), ib.in_dtype == MGI_DTYPE_FP16, (h8 *)y,
                                  (int)ib.shape.pixels(), ib.shape.c, bf, st);
@@ -488,6 +498,8 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
             q.dh = nd.conv.dil_h; q.dw = nd.conv.dil_w;
             q.pt = nd.conv.pad_t; q.pl = nd.conv.pad_l;
             q.act = nd.act1;
+            q.xin = direct_input(p, nd.direct_in, B);
+            q.xin_fp16 = q.xin && p.bufs[nd.direct_in].in_dtype == MGI_DTYPE_FP16;
             return launch_depthwise(q, nd.dw_rows, st);
         }
         case NodeKind::Add:

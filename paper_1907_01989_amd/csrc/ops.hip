@@ -18,6 +18,15 @@ namespace kern {
 
 static inline unsigned blocks_for(size_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// log2 of the slices of a pixel that neighbouring lanes take where a kernel
+// reads or writes NHWC arrays: eight slices unless that would leave more than
+// a third of the lanes past the last slice
+static int nhwc_slices(int S) {
+    int ls = 3;
+    while (ls > 0 && ((S + (1 << ls) - 1) >> ls << ls) * 2 > S * 3) --ls;
+    return ls;
+}
+
 LaunchEvents &launch_events() {
     static thread_local LaunchEvents ev;
     return ev;
@@ -27,68 +36,131 @@ LaunchEvents &launch_events() {
 // Depthwise 3x3 convolution, column strips.  A thread owns one output column
 // of one 8-channel slice of one image and R consecutive output rows: it reads
 // the (R-1)*S + 2*D + 1 input rows of its three input columns once (16 bytes
-// each), and every input value feeds all the outputs whose window covers it,
-// accumulating in fp32 with fp16 taps (exact products).  Consecutive lanes
-// take consecutive columns, so each load instruction of a wave covers a
-// contiguous run of one row.  Taps outside the input read a zeroed 16-byte
-// element instead of branching, so all loads are issued unconditionally.
-// Launch: 1-D, thread g -> column g % OW, strip (g / OW) % nstrips, plane
-// g / (OW * nstrips) (plane = slice * N + image); the divisions are
-// reciprocal products with one correction step (divmod_fast), a few
-// instructions instead of an integer division sequence each.
+// each), and every input value feeds all the outputs whose
+// window covers it, accumulating in fp32 with 16-bit taps (exact products).
+// Taps outside the input read a zeroed element instead of branching, so all
+// loads are issued unconditionally: all of a strip's before its first FMA, or
+// one row ahead of the FMAs for the 32-byte elements of an fp32 input (too
+// many registers).
+// SRC: where the input lies.  0: sliced, [S][N*H*W]; consecutive lanes take
+// consecutive columns, so each load instruction of a wave covers a contiguous
+// run of one row.  1 (fp16), 2 (fp32): the NHWC graph input itself, rounded to
+// the storage type on the way (as the conversion kernel would), C a multiple
+// of 8; 2^ls consecutive lanes take the slices of one pixel and the next ones
+// the next column, so with eight slices loads are whole lines of the NHWC
+// array and stores eight consecutive elements of each slice.  This saves the
+// conversion kernel and its pass over memory (64 x 14 x 14 x 512: fp16 6.8 +
+// 8.2 -> 11.0 us, fp32 -> 11.7; one 56 x 56 x 128 image 4.1 + 4.2 -> 4.2 us).
+// Launch: 1-D, thread g -> slice of its group g % 2^ls, column, strip, then
+// plane (slice group * N + image); the divisions are reciprocal products with
+// one correction step (divmod_fast), a few instructions instead of an integer
+// division sequence each.
 // ---------------------------------------------------------------------------
-template <typename E, int S_, int D_, int R>
+template <typename E, int SRC>
+struct DwElem;   // one element as loaded, and as the storage type
+template <typename E>
+struct DwElem<E, 0> {
+    h8 v;
+    __device__ h8 get() const { return v; }
+};
+template <typename E>
+struct DwElem<E, 1> {
+    h8 v;
+    __device__ h8 get() const {
+        if (!E::bf) return v;
+        float f[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) f[c] = (float)v[c];
+        return E::pack(f);
+    }
+};
+template <typename E>
+struct DwElem<E, 2> {
+    f4 v[2];
+    __device__ h8 get() const {
+        const float f[8] = {v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]};
+        return E::pack(f);
+    }
+};
+
+template <typename E, int S_, int D_, int R, int SRC>
 __global__ __launch_bounds__(256) void dw3_kernel(DwParams p, int nstrips, DivConsts dc) {
-    constexpr int NR = (R - 1) * S_ + 2 * D_ + 1;
-    const int g = blockIdx.x * 256 + threadIdx.x;
+    constexpr int K = 3, NR = (R - 1) * S_ + (K - 1) * D_ + 1;
+    constexpr bool AHEAD = SRC != 2;                       // every load first
+    typedef DwElem<E, SRC> El;
+    int g = blockIdx.x * 256 + threadIdx.x;
     int rest, ox, plane, strip, s, img;
+    int sl = 0;
+    if (SRC) {
+        sl = g & ((1 << p.ls) - 1);
+        g >>= p.ls;
+    }
     divmod_fast(g, p.OW, dc.inv_ow, rest, ox);
     divmod_fast(rest, nstrips, dc.inv_nstrips, plane, strip);
-    if (plane >= p.S * p.N) return;
     divmod_fast(plane, p.N, dc.inv_n, s, img);
-    (void)img;
+    if (SRC) s = (s << p.ls) + sl;
+    if (s >= p.S) return;
+    if (SRC) plane = s * p.N + img;
     const int oy0 = strip * R;
-    const h8 *xin = p.x + (size_t)plane * p.H * p.W;
-    const h8 *wp = p.w + (size_t)s * 9;
-    h8 w[9];
+    const El *xin = SRC ? (const El *)p.xin + (size_t)img * p.H * p.W * p.S + s
+                        : (const El *)p.x + (size_t)plane * p.H * p.W;
+    const int px = SRC ? p.S : 1;                          // elements between neighbouring pixels
+    const h8 *wp = p.w + (size_t)s * (K * K);
+    h8 w[K * K];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) w[t] = wp[t];
+    for (int t = 0; t < K * K; ++t) w[t] = wp[t];
     const int iy0 = oy0 * S_ - p.pt, ix0 = ox * S_ - p.pl;
-    int cx[3];
-    bool cv[3];
+    int cx[K];
+    bool cv[K];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < K; ++k) {
         cx[k] = ix0 + k * D_;
         cv[k] = cx[k] >= 0 && cx[k] < p.W;
     }
-    h8 v[NR][3];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
+    auto load_row = [&](int r, El *v) {
         const int iy = iy0 + r;
         const bool rv = iy >= 0 && iy < p.H;
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-            v[r][k] = *((rv && cv[k]) ? xin + (size_t)iy * p.W + cx[k] : p.zero);
-    }
-    // accumulation per output: bias, then taps ky = 0..2, kx = 0..2 (the
+        for (int k = 0; k < K; ++k)
+            v[k] = *((rv && cv[k]) ? xin + ((size_t)iy * p.W + cx[k]) * px : (const El *)p.zero);
+    };
+    // accumulation per output: bias, then taps ky, kx in window order (the
     // first tap takes the bias as its addend)
     float bias[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) bias[c] = p.bias[s * 8 + c];
     float acc[R][8];
+    auto row_fma = [&](int r, const El *e) {
+        h8 v[K];
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
+        for (int k = 0; k < K; ++k) v[k] = e[k].get();
 #pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
+        for (int ky = 0; ky < K; ++ky) {
             const int t = r - ky * D_;
             if (t >= 0 && t % S_ == 0 && t / S_ < R) {
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    if (ky == 0 && k == 0) E::fma8_from(acc[t / S_], bias, w[0], v[r][0]);
-                    else E::fma8(acc[t / S_], w[ky * 3 + k], v[r][k]);
+                for (int k = 0; k < K; ++k) {
+                    if (ky == 0 && k == 0) E::fma8_from(acc[t / S_], bias, w[0], v[0]);
+                    else E::fma8(acc[t / S_], w[ky * K + k], v[k]);
                 }
             }
         }
+    };
+    if constexpr (AHEAD) {
+        El v[NR][K];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) load_row(r, v[r]);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) row_fma(r, v[r]);
+    } else {
+        El v[2][K];
+        load_row(0, v[0]);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            if (r + 1 < NR) load_row(r + 1, v[(r + 1) & 1]);
+            row_fma(r, v[r & 1]);
+        }
+    }
     // activation as one clamp: [lo, hi] = (-inf, inf), (0, inf) or (0, 6)
     const float lo = p.act == MGI_ACT_NONE ? -INFINITY : 0.0f;
     const float hi = p.act == MGI_ACT_RELU6 ? 6.0f : INFINITY;
@@ -100,6 +172,116 @@ __global__ __launch_bounds__(256) void dw3_kernel(DwParams p, int nstrips, DivCo
 #pragma unroll
         for (int c = 0; c < 8; ++c) q[c] = __builtin_amdgcn_fmed3f(acc[o][c], lo, hi);
         yout[(size_t)(oy0 + o) * p.OW] = E::pack(q);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Depthwise 5x5 convolution from LDS.  A 5x5 strip's loads are too many to
+// hold in registers, and loaded a row ahead of their use they expose one
+// memory latency per input row (16 x 28 x 28 x 240: 12.4 us; one output per
+// thread, as the any-window kernel does, 13.8).  Here a workgroup stages the
+// input rows of a band of output rows, for 2^ls slices of one image, all loads
+// in flight together, with the zero padding written around them, and computes
+// from there: a thread owns four channels (half an element, so that its 25
+// taps fit in registers also when bf16 ones are widened to fp32) of one output
+// column and R rows.  Bound by vector issue (25 * 8 FMAs per output element,
+// 2.1 us of the chip's at this size) and the staging round trip before it:
+// 10.8 us from the NHWC input of either type, and nothing for the conversion
+// (7.5 us fp16, 10.2 fp32); 11.0 with bf16 storage (16.2); one image 4.9
+// (7.7).  SRC as above.
+// ---------------------------------------------------------------------------
+template <typename E, int S_, int SRC>
+__global__ __launch_bounds__(256) void dw5_kernel(DwParams p, DwTile q) {
+    constexpr int K = 5, R = 4 / S_, NR = (R - 1) * S_ + K;
+    typedef DwElem<E, SRC> El;
+    extern __shared__ h8 lds[];
+    const int tid = threadIdx.x, TS = 1 << p.ls;
+    const int nband = q.nbands, b = blockIdx.x % nband, rest = blockIdx.x / nband;
+    const int n = rest % p.N, s0 = (rest / p.N) << p.ls;
+    const int nsl = min(TS, p.S - s0);
+    const int oy0 = b * q.rb, rows = min(q.rb, p.OH - oy0);
+    const int nrb = (rows - 1) * S_ + K, wp = q.wp;         // band: [TS][nrb][wp], first column -pl
+    const int iy0 = oy0 * S_ - p.pt;
+    h8 *taps = lds + TS * q.nrb * wp;                        // [TS][25]
+    // taps and the band; cells outside the input are zero
+    for (int e = tid; e < nsl * K * K; e += 256) taps[e] = p.w[(size_t)s0 * (K * K) + e];
+    const El *xin = SRC ? (const El *)p.xin + (size_t)n * p.H * p.W * p.S + s0
+                        : (const El *)p.x + ((size_t)s0 * p.N + n) * p.H * p.W;
+    const size_t xs = SRC ? 1 : (size_t)p.N * p.H * p.W;     // elements between slices
+    const int px = SRC ? p.S : 1;                            // ... and between neighbouring pixels
+    const int cells = nsl * nrb * wp;
+    constexpr int U = SRC == 2 ? 4 : 8;
+    for (int e0 = tid; e0 < cells; e0 += 256 * U) {
+        El v[U];
+        int at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * 256;
+            int sl, r, c, t;
+            if (SRC) {                                       // slice fastest
+                divmod_fast(min(e, cells - 1), nsl, q.inv_nsl[nsl == TS ? 0 : 1], t, sl);
+                divmod_fast(t, wp, q.inv_wp, r, c);
+            } else {                                         // column fastest
+                divmod_fast(min(e, cells - 1), wp, q.inv_wp, t, c);
+                divmod_fast(t, nrb, rows == q.rb ? q.inv_nrb[0] : q.inv_nrb[1], sl, r);
+            }
+            const int iy = iy0 + r, ix = c - p.pl;
+            const bool in = iy >= 0 && iy < p.H && ix >= 0 && ix < p.W;
+            v[u] = *(in ? xin + xs * sl + ((size_t)iy * p.W + ix) * px : (const El *)p.zero);
+            at[u] = e < cells ? (sl * nrb + r) * wp + c : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (at[u] >= 0) lds[at[u]] = v[u].get();
+    }
+    __syncthreads();
+
+    const float lo = p.act == MGI_ACT_NONE ? -INFINITY : 0.0f;
+    const float hi = p.act == MGI_ACT_RELU6 ? 6.0f : INFINITY;
+    const int nstrip = (rows + R - 1) / R, ntask = nsl * nstrip * p.OW * 2;
+    for (int t0 = tid; t0 < ntask; t0 += 256) {
+        const int half = t0 & 1;
+        int t, ox;
+        divmod_fast(t0 >> 1, p.OW, q.inv_ow, t, ox);
+        const int sl = t / nstrip, strip = t - sl * nstrip;
+        const h4 *w4 = (const h4 *)(taps + sl * (K * K)) + half;
+        h4 w[K * K];
+#pragma unroll
+        for (int i = 0; i < K * K; ++i) w[i] = w4[2 * i];
+        float bias[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) bias[c] = p.bias[(s0 + sl) * 8 + half * 4 + c];
+        float acc[R][4];
+        const h4 *row = (const h4 *)(lds + (sl * nrb + strip * R * S_) * wp + ox * S_) + half;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            // (rows past the band belong to outputs past it, never stored: they
+            // read the band's last row)
+            const h4 *rp = row + (size_t)min(r, nrb - 1 - strip * R * S_) * wp * 2;
+            h4 v[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) v[k] = rp[2 * k];
+#pragma unroll
+            for (int ky = 0; ky < K; ++ky) {
+                const int o = r - ky;
+                if (o >= 0 && o % S_ == 0 && o / S_ < R) {
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        if (ky == 0 && k == 0) E::fma4_from(acc[o / S_], bias, w[0], v[0]);
+                        else E::fma4(acc[o / S_], w[ky * K + k], v[k]);
+                    }
+                }
+            }
+        }
+        h4 *yout = (h4 *)(p.y + (((size_t)(s0 + sl) * p.N + n) * p.OH + oy0 + strip * R) * p.OW + ox) + half;
+#pragma unroll
+        for (int o = 0; o < R; ++o) {
+            if (strip * R + o >= rows) break;
+            float z[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) z[c] = __builtin_amdgcn_fmed3f(acc[o][c], lo, hi);
+            yout[(size_t)o * p.OW * 2] = E::pack4(z);
+        }
     }
 }
 
@@ -136,20 +318,74 @@ __global__ __launch_bounds__(256) void dw_kernel(DwParams p, int tpp) {
 }
 
 template <typename E, int S_, int D_, int R>
-static hipError_t launch_dw3(const DwParams &p, hipStream_t st) {
+static hipError_t launch_dw3(DwParams p, hipStream_t st) {
     const int nstrips = (p.OH + R - 1) / R;
-    const size_t threads = (size_t)p.OW * nstrips * p.S * p.N;
+    p.ls = p.xin ? nhwc_slices(p.S) : 0;
+    const size_t slices = ((size_t)p.S + (1 << p.ls) - 1) >> p.ls << p.ls;
+    const size_t threads = (size_t)p.OW * nstrips * slices * p.N;
     if (threads > 0x7fffffffull) return hipErrorInvalidValue;
     const DivConsts dc{1.0 / p.OW, 1.0 / nstrips, 1.0 / p.N};
-    launch((dw3_kernel<E, S_, D_, R>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
-           p, nstrips, dc);
+    const dim3 grid((unsigned)((threads + 255) / 256)), block(256);
+    if (!p.xin) launch((dw3_kernel<E, S_, D_, R, 0>), grid, block, 0, st, p, nstrips, dc);
+    else if (p.xin_fp16) launch((dw3_kernel<E, S_, D_, R, 1>), grid, block, 0, st, p, nstrips, dc);
+    else launch((dw3_kernel<E, S_, D_, R, 2>), grid, block, 0, st, p, nstrips, dc);
     return hipGetLastError();
+}
+
+// Band of the 5x5 kernel: as many slices (up to eight) and then strips (up to
+// two) per workgroup as keep 64 KiB of LDS and two workgroups per compute unit
+// (fewer, where even one slice and strip give less); 0 slices: no band fits.
+static DwTile dw5_tile(int N, int S, int OH, int OW, int sh, int &ls) {
+    DwTile t{};
+    const int R = 4 / sh;
+    t.wp = (OW - 1) * sh + 5;
+    auto lds = [&](int l, int rb) { return (size_t)(1 << l) * (((size_t)(rb - 1) * sh + 5) * t.wp + 25) * 16; };
+    auto wgs = [&](int l, int rb) { return (((size_t)S + (1 << l) - 1) >> l) * N * ((OH + rb - 1) / rb); };
+    ls = nhwc_slices(S);
+    while (ls > 0 && (lds(ls, R) > 65536 || wgs(ls, R) < 512)) --ls;
+    t.rb = lds(ls, 2 * R) <= 65536 && wgs(ls, 2 * R) >= 512 ? 2 * R : R;
+    t.nrb = (t.rb - 1) * sh + 5;
+    t.nbands = (OH + t.rb - 1) / t.rb;
+    t.lds = lds(ls, t.rb);
+    if (t.lds > 65536 || wgs(ls, t.rb) > 0x7fffffffull) t.nbands = 0;
+    return t;
+}
+
+template <typename E, int S_>
+static hipError_t launch_dw5(DwParams p, DwTile t, hipStream_t st) {
+    const int last = p.OH - (t.nbands - 1) * t.rb;          // rows of the last band
+    const int tail = p.S - ((p.S - 1) >> p.ls << p.ls);     // slices of the last group
+    t.inv_wp = 1.0 / t.wp;
+    t.inv_ow = 1.0 / p.OW;
+    t.inv_nsl[0] = 1.0 / (1 << p.ls);
+    t.inv_nsl[1] = 1.0 / tail;
+    t.inv_nrb[0] = 1.0 / t.nrb;
+    t.inv_nrb[1] = 1.0 / ((last - 1) * p.sh + 5);
+    const dim3 grid((unsigned)(t.nbands * p.N * ((p.S + (1 << p.ls) - 1) >> p.ls))), block(256);
+    if (!p.xin) launch((dw5_kernel<E, S_, 0>), grid, block, (unsigned)t.lds, st, p, t);
+    else if (p.xin_fp16) launch((dw5_kernel<E, S_, 1>), grid, block, (unsigned)t.lds, st, p, t);
+    else launch((dw5_kernel<E, S_, 2>), grid, block, (unsigned)t.lds, st, p, t);
+    return hipGetLastError();
+}
+
+static bool dw3_window(int KH, int KW, int sh, int sw, int dh, int dw) {
+    return KH == 3 && KW == 3 && sh == sw && dh == dw && sh >= 1 && sh <= 2 && dh >= 1 && dh <= 2;
+}
+
+static bool dw5_window(int KH, int KW, int sh, int sw, int dh, int dw) {
+    return KH == 5 && KW == 5 && sh == sw && dh == 1 && dw == 1 && sh >= 1 && sh <= 2;
+}
+
+bool depthwise_reads_nhwc(int KH, int KW, int sh, int sw, int dh, int dw, int N, int S, int OH, int OW) {
+    int ls;
+    return dw3_window(KH, KW, sh, sw, dh, dw) ||
+           (dw5_window(KH, KW, sh, sw, dh, dw) && dw5_tile(N, S, OH, OW, sh, ls).nbands > 0);
 }
 
 hipError_t launch_depthwise(const DwParams &p, int rows, hipStream_t st) {
     const int ohw = p.OH * p.OW;
     if (ohw <= 0 || p.N <= 0 || p.S <= 0) return hipSuccess;
-    if (p.KH == 3 && p.KW == 3 && p.sh == p.sw && p.dh == p.dw) {
+    if (dw3_window(p.KH, p.KW, p.sh, p.sw, p.dh, p.dw)) {
         // output rows per thread: 4 at stride 1, 2 at stride 2 unless chosen
         const int R = rows > 0 ? rows : (p.sh == 1 ? 4 : 2);
 #define MGI_DW_CASE(S_, D_, R_) \
@@ -162,6 +398,15 @@ hipError_t launch_depthwise(const DwParams &p, int rows, hipStream_t st) {
 #undef MGI_DW_CASE
         if (rows > 0) return hipErrorInvalidValue;
     }
+    if (dw5_window(p.KH, p.KW, p.sh, p.sw, p.dh, p.dw)) {
+        DwParams q = p;
+        const DwTile t = dw5_tile(p.N, p.S, p.OH, p.OW, p.sh, q.ls);
+        if (t.nbands > 0) {
+            if (p.sh == 1) return p.bf16 ? launch_dw5<BF16, 1>(q, t, st) : launch_dw5<F16, 1>(q, t, st);
+            return p.bf16 ? launch_dw5<BF16, 2>(q, t, st) : launch_dw5<F16, 2>(q, t, st);
+        }
+    }
+    if (p.xin) return hipErrorInvalidValue;
     const int tpp = (ohw + 255) / 256;
     const size_t nblk = (size_t)tpp * p.S * p.N;
     if (nblk > 0x7fffffffu) return hipErrorInvalidValue;
@@ -600,14 +845,12 @@ __global__ __launch_bounds__(256) void export_kernel(const h8 *x, float *y, unsi
     }
 }
 
-// Slices of a wave (2^ls) and grid for S slices of M pixels: eight slices
-// unless that would leave more than a third of the lanes past the last slice;
-// four pixels per thread once one pixel per thread gives more than eight
+// Slices of a wave (2^ls) and grid for S slices of M pixels: four pixels per
+// thread once one pixel per thread gives more than eight
 // workgroups per compute unit (fewer, longer threads below that leave compute
 // units idle).  False when the grid does not fit.
 static bool nhwc_grid(int M, int S, int &ls, int &U, int &sgroups, unsigned &grid) {
-    ls = 3;
-    while (ls > 0 && ((S + (1 << ls) - 1) >> ls << ls) * 2 > S * 3) --ls;
+    ls = nhwc_slices(S);
     sgroups = (S + (1 << ls) - 1) >> ls;
     const size_t px = (size_t)4 * (64 >> ls), one = ((size_t)M + px - 1) / px * (size_t)sgroups;
     U = one > 2048 ? 4 : 1;

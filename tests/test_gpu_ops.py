@@ -331,3 +331,49 @@ def test_conv_window_every_configuration(n, h, w, cin, cout, k, s, d, pads, res,
             first = outs[0]
             check_isolated("conv", first, ref.reshape(first.shape), rtol=ISO_RTOL_BF16 if dtype else ISO_RTOL)
         np.testing.assert_array_equal(outs[0], first)
+
+
+DW_INPUT_CASES = [
+    # n, h, w, c, k, s, d: depthwise convolutions that read the NHWC graph input
+    (1, 56, 56, 128, 3, 1, 1),
+    (2, 9, 7, 8, 3, 1, 1),            # one slice
+    (3, 13, 11, 24, 3, 2, 1),         # three slices (lanes past the last one)
+    (1, 5, 6, 72, 3, 1, 2),           # nine slices, dilation 2
+    (2, 17, 15, 40, 3, 2, 2),
+    (1, 1, 1, 64, 3, 1, 1),
+    (2, 10, 9, 104, 5, 1, 1),
+    (5, 11, 14, 16, 5, 2, 1),
+    (1, 3, 3, 48, 5, 1, 1),           # a plane smaller than the window
+]
+
+
+@pytest.mark.parametrize("n,h,w,c,k,s,d", DW_INPUT_CASES)
+@pytest.mark.parametrize("src,dtype", [(0, 0), (2, 0), (0, 1), (2, 1)])
+def test_depthwise_reads_the_graph_input(n, h, w, c, k, s, d, src, dtype):
+    """In every configuration, aligned (the kernel reads the input itself) and
+    not (the conversion kernel runs first): the oracle's result, and bit for
+    bit that of a plan that keeps the converted tensor."""
+    import torch
+    from paper_1907_01989_amd import engine, _binding as B
+    g = NetBuilder(seed=c + h)
+    y = g.dw(g.input(n, h, w, c, -1, 1, dtype=src), k, s, d, act=ACT_RELU6)
+    g.mark_output(y)
+    desc = g.graph(f"dwin_{n}x{h}x{w}x{c}_k{k}s{s}d{d}")
+    if dtype:
+        desc = workloads.as_bf16_graph(desc)
+    log(f"[case] {desc['name']} src {src} store {dtype}")
+    ref = oracle.run_graph(desc)[y]
+    _, kept, _ = run_gpu(desc, materialize_all=True, dtype=dtype)
+    check_isolated("dw", kept[0], ref.reshape(kept[0].shape), rtol=ISO_RTOL_BF16 if dtype else ISO_RTOL)
+    plan = engine.Plan(desc, dtype=dtype)
+    i = [m["kind"] for m in plan.nodes()].index("dw_conv")
+    x = plan.input_tensors()[0]
+    for cfg in range(plan.node_configs()[i][1]):
+        B.mgi_plan_set_node_config(plan.handle, i, cfg)
+        for off in (0, 1):
+            xb = torch.empty(x.numel() + off, dtype=x.dtype, device=x.device)
+            xo = xb[off:].view(x.shape)
+            xo.copy_(x)
+            out = plan.run([xo])[0]
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(out.cpu().numpy(), kept[0], err_msg=f"config {cfg} offset {off}")
