@@ -240,7 +240,13 @@ struct PwDwParams {
 struct PwDwGeom {
     int ipt, nbands, groups, nbt, pstride;
     size_t lds;
+    float cost;          // estimated time, us
 };
+// Whether some configuration gets at least 128 workgroups (16-channel bands,
+// which trade work for workgroups most, do not count), and the configuration
+// with the lowest estimate: of those with 128 workgroups where there are any,
+// or (always, or none) of all.
+int pwdw_best(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int ksp, int nb16, bool always, bool *fills);
 // Number of fused-kernel configurations that cover a shape (0: none); for
 // 0 <= cfg < that number, its geometry and name.
 int pwdw_configs(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int ksp, int nb16, int cfg,

@@ -89,11 +89,6 @@ GemmTile pick_tile(size_t M, int cout) {
     return t;
 }
 
-// Pipelined pointwise kernel (K >= 64, at least 64 output channels): a
-// 128 x 128 tile when there are at least 512 channels, else 128 x 64, as long
-// as that still gives 384 workgroups (1.5 per CU); otherwise the shape with
-// the most workgroups.  Measured on the MobileNet shapes: 128-channel tiles
-// pay off only when many channels share one activation read.
 // Candidate kernel configurations of a node for the autotuner; the first is
 // the configuration finalize picked.  Every candidate accumulates each output
 // in the same order (K ascending in steps of 32 for the GEMMs, taps in window
@@ -106,6 +101,7 @@ std::string tile_name(const GemmTile &t) {
 }
 
 void pick_pipe_tile(GemmTile &t, size_t M, int npad);
+GemmTile pick_pw_tile(size_t M, int npad, int ksl, int ksp);
 
 // Windowed convolution through the ring: 64 x 64 tiles, except where another
 // shape measured faster (3x3, us):
@@ -220,6 +216,8 @@ void add_pwdw_configs(Node &nd) {
         Node::Config fc{GemmTile{}, 0, name, false, c};
         nd.cfgs.push_back(fc);
     }
+    // the lowest estimate first, the others in table order
+    std::rotate(nd.cfgs.begin(), nd.cfgs.begin() + nd.pwdw_first, nd.cfgs.begin() + nd.pwdw_first + 1);
     GemmTile t;
     pick_pipe_tile(t, nd.dw_in.pixels(), nd.nb16 * 16);
     const int dwr = nd.dw_conv.stride_h == 1 ? 4 : 2;
@@ -338,25 +336,48 @@ void add_fc_configs(Node &nd, size_t M) {
     nd.apply(0);
 }
 
+// The pooled GEMM's default tile for N images of hw pixels: 128-row tiles when
+// they give at least 128 workgroups (128 channels wide from K = 512 on, where
+// those still do: 64 images of 7 x 7 x 1024 -> 1024 13.6 us against 14.5 for
+// 128 x 64), else 64 x 64 with two K-steps per stage where K allows (14 such
+// images 10.3 us against 11.9 for 128 x 64, 7 images 9.5 / 11.5).
+GemmTile pick_pool_tile(int N, int hw, int npad, int ksp) {
+    GemmTile t;
+    t.pipe = true;
+    if (hw < 1 || hw > 64) return t;
+    const size_t groups = ((size_t)N + 128 / hw - 1) / (128 / hw);
+    if (groups * (size_t)((npad + 63) / 64) >= 128) {
+        t.bm = 128;
+        if (ksp >= 64 && npad > 64 && groups * (size_t)((npad + 127) / 128) >= 128) t.bn = 128;
+    } else if (ksp % 8 == 0) {
+        t.ks = 8;
+    }
+    return t;
+}
+
+// workgroups of that tile
+size_t pool_workgroups(const GemmTile &t, int N, int hw, int npad) {
+    const size_t ipt = std::max(1, t.bm / hw);
+    return ((size_t)N + ipt - 1) / ipt * (size_t)((npad + t.bn - 1) / t.bn);
+}
+
 void add_pool_configs(Node &nd) {
     // tiles of the pooled GEMM (M-tiles of whole images), and the GEMM
     // then the pool kernel through the scratch tensor (first when the
     // fused kernel would not fill the GPU)
     const int hw = nd.dw_in.h * nd.dw_in.w, npad = nd.nb16 * 16;
-    const int tiles[4][2] = {{128, 64}, {128, 128}, {64, 128}, {64, 64}};
+    const GemmTile first = pick_pool_tile(nd.dw_in.n, hw, npad, nd.ksp);
+    const int tiles[5][3] = {{128, 64, 4}, {128, 128, 4}, {64, 128, 4}, {64, 64, 4}, {64, 64, 8}};
     for (auto &tb : tiles) {
-        if (hw > tb[0] || (tb[1] > 64 && npad <= 64)) continue;
+        if (hw > tb[0] || (tb[1] > 64 && npad <= 64) || nd.ksp % tb[2] != 0) continue;
         GemmTile t;
         t.pipe = true;
         t.bm = tb[0];
         t.bn = tb[1];
-        nd.cfgs.push_back({t, 0, "pool" + std::to_string(tb[0]) + "x" + std::to_string(tb[1])});
-    }
-    if (nd.ksp % 8 == 0) {
-        GemmTile t;
-        t.pipe = true;
-        t.ks = 8;
-        nd.cfgs.push_back({t, 0, "pool64x64k8"});
+        t.ks = tb[2];
+        const Node::Config c{t, 0, "pool" + std::to_string(t.bm) + "x" + std::to_string(t.bn) + (t.ks == 8 ? "k8" : "")};
+        const bool lead = t.bm == first.bm && t.bn == first.bn && t.ks == first.ks;
+        nd.cfgs.insert(lead ? nd.cfgs.begin() : nd.cfgs.end(), c);
     }
     // weight-slab tiles of one 64-row image group (planes of at most 64
     // pixels) for grids of few workgroups: the slab loads in one round and
@@ -493,11 +514,13 @@ void fuse_pw_into_dw(mgi_plan &p, bool always) {
         Node &pw = p.nodes[producer[mid]];
         if (pw.kind != NodeKind::Gemm || pw.taps || pw.residual >= 0 || pw.in.size() != 1) continue;
         const Shape in = p.bufs[mid].shape, out = p.bufs[dw.out].shape;
-        kern::PwDwGeom geo{};
-        if (kern::pwdw_configs(in.n, in.h, in.w, out.h, out.w, c.stride_h, c.pad_t, c.pad_l, pw.ksp, pw.nb16, 0, &geo,
-                               nullptr) == 0)
+        if (kern::pwdw_configs(in.n, in.h, in.w, out.h, out.w, c.stride_h, c.pad_t, c.pad_l, pw.ksp, pw.nb16, -1,
+                               nullptr, nullptr) == 0)
             continue;
-        pw.fused_default = always || (size_t)geo.groups * ((pw.nb16 + geo.nbt - 1) / geo.nbt) >= 128;
+        bool fills = false;
+        pw.pwdw_first = kern::pwdw_best(in.n, in.h, in.w, out.h, out.w, c.stride_h, c.pad_t, c.pad_l, pw.ksp, pw.nb16,
+                                        always, &fills);
+        pw.fused_default = always || fills;
         pw.kind = NodeKind::PwDw;
         pw.kname = "pw_dw";
         pw.dw_op = dw.op;
@@ -651,8 +674,8 @@ void fuse_pool_into_pw(mgi_plan &p, bool always) {
             continue;
         const Shape in = p.bufs[mid].shape;
         if (in.h * in.w > 64 || pw.ksp % 4 != 0) continue;
-        const int hw = in.h * in.w, ipt = 128 / hw;
-        pw.fused_default = always || (size_t)((in.n + ipt - 1) / ipt) * ((pw.nb16 * 16 + 63) / 64) >= 128;
+        const int hw = in.h * in.w, npad = pw.nb16 * 16;
+        pw.fused_default = always || pool_workgroups(pick_pool_tile(in.n, hw, npad, pw.ksp), in.n, hw, npad) >= 128;
         pw.kind = NodeKind::GemmPool;
         pw.kname = "pw_pool";
         pw.dw_in = in;
@@ -707,21 +730,60 @@ void fuse_softmax_into_fc(mgi_plan &p) {
     p.nodes.swap(kept);
 }
 
+// Pipelined pointwise kernel (K >= 64, at least 64 output channels): a
+// 128 x 128 tile when there are at least 512 channels, else 128 x 64, as long
+// as that still gives 384 workgroups (1.5 per CU); otherwise 64 x 64, which
+// makes the most.  Measured on the MobileNet shapes: 128-channel tiles pay off
+// only when many channels share one activation read.
 void pick_pipe_tile(GemmTile &t, size_t M, int npad) {
     const int cand[3][2] = {{128, 128}, {128, 64}, {64, 64}};
-    size_t best_tiles = 0;
     int best = 2;
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < 2; ++c) {
         const int bm = cand[c][0], bn = cand[c][1];
         if (bn == 128 && npad < 512) continue;
         const size_t tiles = ((M + bm - 1) / bm) * (size_t)((npad + bn - 1) / bn);
         if (tiles >= 384) { best = c; break; }
-        if (tiles > best_tiles) { best_tiles = tiles; best = c; }
     }
     t.pipe = true;
     t.slab = false;
     t.bm = cand[best][0];
     t.bn = cand[best][1];
+}
+
+// Pointwise convolution of M pixels, npad channels, ksl (padded ksp) K slices:
+//  - grids of under one 64 x 16 tile per compute unit with K >= 256: the
+//    16-channel weight slab with the 8-step prefetch (784 x 464 -> 160 4.4 us
+//    against 7.2 for the pipelined 64 x 64 tile, 49 x 960 -> 160 4.6 / 6.5,
+//    576 x 256 -> 256 4.0 / 6.0);
+//  - K >= 64 and at least 64 channels: the pipelined kernel;
+//  - else a 32-channel weight slab with 128-pixel tiles, or 64-pixel ones where
+//    those leave compute units idle (400 x 96 -> 24 4.0 / 6.0), two K steps of
+//    prefetch when there are at least two; and where the slab does not fit
+//    64 KiB (K above 768) the pipelined 64 x 64 tile, half of it empty
+//    (10192 x 864 -> 24 7.5 us against 16.4 for the LDS-staged 32 x 32 tile).
+GemmTile pick_pw_tile(size_t M, int npad, int ksl, int ksp) {
+    GemmTile t;
+    if (ksp >= 32 && (M + 63) / 64 * (size_t)(npad / 16) < 256 && kern::gemm_xs_lds_bytes(ksp, 16, 16) <= 160 * 1024) {
+        t.slab = true;
+        t.wm = 16;
+        t.bn = 16;
+        t.pf = 8;
+        return t;
+    }
+    if (ksl >= 8 && npad >= 64) {
+        pick_pipe_tile(t, M, npad);
+        return t;
+    }
+    const int wm = (M + 127) / 128 * (size_t)((npad + 31) / 32) >= 256 ? 32 : 16;
+    if (kern::gemm_xs_lds_bytes(ksp, wm, 32) > 65536) {
+        t.pipe = true;
+        return t;
+    }
+    t.slab = true;
+    t.wm = wm;
+    t.bn = 32;
+    t.pf = ksp >= 8 ? 2 : 1;
+    return t;
 }
 
 }  // namespace
@@ -1038,20 +1100,8 @@ mgi_status Lowering::lower_conv(const Group &G, const GOp &op, const Shape &out_
     if (nd.kind == NodeKind::Gemm && nd.taps && nd.ksp % 8 == 0 &&
         kern::conv_pipe_ok(d.kh, d.kw, nd.ksp, x.h, x.w, out_shape.h, out_shape.w)) {
         nd.tile = pick_conv_tile(out_shape.pixels(), nd.nb16 * 16);
-    } else if (nd.kind == NodeKind::Gemm && !nd.taps && nd.ksl >= 8 && nd.nb16 * 16 >= 64) {
-        pick_pipe_tile(nd.tile, out_shape.pixels(), nd.nb16 * 16);
     } else if (nd.kind == NodeKind::Gemm && !nd.taps) {
-        // weight-slab kernel: 128 x 32 tiles, two K steps of
-        // prefetch when there are at least two; the slab (32
-        // channels x all K) plus the epilogue tiles fit 64 KiB
-        // up to K = 768
-        const size_t slab = (size_t)2 * nd.ksp * 256 + 16384;
-        if (slab <= 65536) {
-            nd.tile.slab = true;
-            nd.tile.wm = 32;
-            nd.tile.bn = 32;
-            nd.tile.pf = nd.ksp >= 8 ? 2 : 1;
-        }
+        nd.tile = pick_pw_tile(out_shape.pixels(), nd.nb16 * 16, nd.ksl, nd.ksp);
     }
     if (G.residual_tensor >= 0) {
         int rb = need_c8(G.residual_tensor);

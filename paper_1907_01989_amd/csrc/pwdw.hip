@@ -31,6 +31,7 @@
 // separate GEMM and depthwise kernels, so the result is bit-identical to the
 // unfused pair (and to the node's split form, which runs those kernels).
 #include <algorithm>
+#include <cmath>
 #include <utility>
 
 #include "device.h"
@@ -343,7 +344,7 @@ struct Inst {
     int ipt = 0;   // image tiles: images per workgroup (0: as many as fit)
 };
 
-// the candidates, in preference order for a shape
+// the candidates (their order breaks ties of the estimate below)
 constexpr Inst kInsts[] = {
     {false, 8, 2, 4, 1, 7, 16, 4, "img64"},   {false, 8, 2, 8, 1, 7, 16, 4, "img128"},
     {false, 8, 2, 4, 1, 7, 8, 4, "img64"},    {false, 8, 2, 8, 1, 7, 8, 4, "img128"},
@@ -420,6 +421,31 @@ size_t lds_bytes(const Inst &in, int ksp, int pstride) {
     return (slab > otile ? slab : otile) + tail_bytes(in.nbt);
 }
 
+// Estimated time, us, of an instance on a grid of W workgroups: a fixed part;
+// the work of the workgroups that share a compute unit, one after the other
+// (weight slab per KiB, MFMAs per SIMD, activation loads per wave KiB,
+// depthwise passes per SIMD), times their number (whole ones up to four, the
+// start and end of rounds blur beyond); and what one workgroup's serial chain
+// adds.  Fitted to 215 shapes (v1's and v2's layers at 96 to 224 pixels,
+// batches of 1 to 64, and expansions of 16 to 320 channels on 5 to 112 wide
+// planes), every instance timed in whole runs: the instance with the lowest
+// estimate is 2.7% slower than the best one in the geometric mean, the first
+// applicable one of the table 39%.
+float cost_us(const Inst &in, const PwDwGeom &g, int N, int H, int W, int OH, int ksp, int nb16) {
+    const int nk = ksp / 4;
+    const float wgs = (float)g.groups * ((nb16 + in.nbt - 1) / in.nbt), per = wgs / 256.0f;
+    const float share = per <= 1.0f ? 1.0f : per <= 4.0f ? std::ceil(per) : per + 0.5f;
+    const int imgs = std::min(g.ipt, N), pixels = in.band ? g.pstride : imgs * H * W;
+    const int frags = ((pixels + 15) / 16 + in.nw - 1) / in.nw;              // the busiest wave's
+    const int strips = in.band ? 1 : (OH + in.r - 1) / in.r;
+    const int passes = (imgs * 2 * in.nbt * strips + in.nw * 64 / in.lpr - 1) / (in.nw * 64 / in.lpr);
+    const float simd = in.nw / 4.0f, dw = passes * (in.r + 3.2f);
+    const float slab_kib = (float)((nk + in.pf - 1) / in.pf * in.pf) * in.nbt;
+    const float work = 0.0176f * slab_kib + 0.0092f * nk * frags * in.nbt * simd + 0.003f * nk * frags * in.nw +
+                       0.157f * dw * simd;
+    return 4.0f + share * work + 0.0009f * nk * frags * in.nbt + 0.046f * dw;
+}
+
 // geometry of instance `in` for a shape, or false if it does not apply
 bool fits(const Inst &in, int N, int H, int W, int OH, int OW, int S, int pt, int pl, int ksp, int nb16,
           PwDwGeom *g) {
@@ -459,6 +485,7 @@ bool fits(const Inst &in, int N, int H, int W, int OH, int OW, int S, int pt, in
     }
     g->nbt = in.nbt;
     g->lds = lds_bytes(in, ksp, g->pstride);
+    g->cost = cost_us(in, *g, N, H, W, OH, ksp, nb16);
     return g->lds <= (size_t)kPwDwLds;
 }
 
@@ -509,6 +536,22 @@ int applicable(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int k
     return n;
 }
 }  // namespace
+
+int pwdw_best(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int ksp, int nb16, bool always,
+              bool *fills) {
+    int idx[kNumInsts];
+    PwDwGeom geo[kNumInsts];
+    const int n = applicable(N, H, W, OH, OW, S, pt, pl, ksp, nb16, idx, geo);
+    auto wgs = [&](int c) { return geo[c].groups * ((nb16 + geo[c].nbt - 1) / geo[c].nbt); };
+    *fills = false;
+    for (int c = 0; c < n; ++c) *fills |= wgs(c) >= 128 && !(kInsts[idx[c]].band && geo[c].nbt == 1);
+    int best = -1;
+    for (int c = 0; c < n; ++c) {
+        if (*fills && !always && wgs(c) < 128) continue;
+        if (best < 0 || geo[c].cost < geo[best].cost) best = c;
+    }
+    return best;
+}
 
 int pwdw_configs(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int ksp, int nb16, int cfg,
                  PwDwGeom *g, const char **name) {

@@ -587,3 +587,51 @@ def test_grid_dependent_candidates():
             assert all(x.endswith("p8") for x in slabs if "x16" in x)
             if not few and n["shape"][1] >= 28:
                 assert not any(x.endswith("p8") for x in slabs)
+
+
+def _one_pair(n, h, w, k, c, s):
+    g = NetBuilder(seed=0)
+    g.mark_output(g.dw(g.conv(g.input(n, h, w, k, -1, 1), c), 3, s))
+    return g.graph("pair")
+
+
+@pytest.mark.parametrize("n,h,w,k,c,s,fused", [
+    (1, 14, 14, 512, 512, 1, False),      # 32 workgroups at most
+    (7, 14, 14, 512, 512, 1, True),       # 16-channel image tiles: 224
+    (1, 56, 56, 64, 128, 1, False),       # 224 only as 16-channel bands, which do not count
+    (2, 56, 56, 24, 144, 1, True),
+    (64, 14, 14, 512, 512, 1, True),
+    (5, 15, 15, 96, 576, 2, True),
+])
+def test_pair_default_configuration(n, h, w, k, c, s, fused):
+    # the fused kernel is listed first exactly where some tiling of it (but
+    # 16-channel bands) gets 128 workgroups or it is asked for; every
+    # configuration is listed once, whichever comes first
+    desc = _one_pair(n, h, w, k, c, s)
+    for always in (1, 2):
+        plan = engine.Plan(desc, bind=False, fuse_pwdw=always)
+        i = [m["kind"] for m in plan.nodes()].index("pw_dw")
+        names = _config_names(plan, i)
+        assert len(set(names)) == len(names)
+        assert names[0].startswith(("img", "band")) == (fused or always == 2), names
+        if always == 1:
+            first = names
+    assert sorted(first) == sorted(names)
+
+
+@pytest.mark.parametrize("m,k,c,name", [
+    (784, 464, 160, "slab64x16p8"),       # under one 64x16 tile per compute unit, K >= 256
+    (49 * 64, 960, 160, "pipe64x64"),     # 490 such tiles
+    (49, 128, 256, "pipe64x64"),          # K < 256
+    (400, 96, 24, "slab64x32p2"),         # 128-pixel slabs would leave compute units idle
+    (64 * 784, 96, 24, "slab128x32p2"),
+    (10192, 864, 24, "pipe64x64"),        # the slab of 32 channels does not fit
+    (12544, 512, 512, "pipe128x128"),
+])
+def test_pointwise_default_tile(m, k, c, name):
+    g = NetBuilder(seed=0)
+    g.mark_output(g.conv(g.input(1, m, 1, k, -1, 1), c))
+    plan = engine.Plan(g.graph("pw"), bind=False)
+    i = [q["kind"] for q in plan.nodes()].index("pw_gemm")
+    names = _config_names(plan, i)
+    assert names[0] == name and len(set(names)) == len(names), names
