@@ -756,11 +756,12 @@ void pick_pipe_tile(GemmTile &t, size_t M, int npad) {
 //    against 7.2 for the pipelined 64 x 64 tile, 49 x 960 -> 160 4.6 / 6.5,
 //    576 x 256 -> 256 4.0 / 6.0);
 //  - K >= 64 and at least 64 channels: the pipelined kernel;
-//  - else a 32-channel weight slab with 128-pixel tiles, or 64-pixel ones where
-//    those leave compute units idle (400 x 96 -> 24 4.0 / 6.0), two K steps of
-//    prefetch when there are at least two; and where the slab does not fit
-//    64 KiB (K above 768) the pipelined 64 x 64 tile, half of it empty
-//    (10192 x 864 -> 24 7.5 us against 16.4 for the LDS-staged 32 x 32 tile).
+//  - else, K above 512: the pipelined 64 x 64 tile, half of it empty
+//    (10192 x 864 -> 24 7.5 us against 9.1 for a 32-channel slab and 16.4 for
+//    the LDS-staged 32 x 32 tile);
+//  - else a 32-channel weight slab with 64-pixel tiles (81920 x 192 -> 32
+//    10.3 us, 128-pixel ones 11.7), or 128-pixel ones for K < 128 where they
+//    fill the compute units; two K steps of prefetch when there are two.
 GemmTile pick_pw_tile(size_t M, int npad, int ksl, int ksp) {
     GemmTile t;
     if (ksp >= 32 && (M + 63) / 64 * (size_t)(npad / 16) < 256 && kern::gemm_xs_lds_bytes(ksp, 16, 16) <= 160 * 1024) {
@@ -774,11 +775,11 @@ GemmTile pick_pw_tile(size_t M, int npad, int ksl, int ksp) {
         pick_pipe_tile(t, M, npad);
         return t;
     }
-    const int wm = (M + 127) / 128 * (size_t)((npad + 31) / 32) >= 256 ? 32 : 16;
-    if (kern::gemm_xs_lds_bytes(ksp, wm, 32) > 65536) {
+    if (ksp > 64) {
         t.pipe = true;
         return t;
     }
+    const int wm = ksp < 16 && (M + 127) / 128 * (size_t)((npad + 31) / 32) >= 256 ? 32 : 16;
     t.slab = true;
     t.wm = wm;
     t.bn = 32;

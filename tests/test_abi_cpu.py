@@ -625,7 +625,8 @@ def test_pair_default_configuration(n, h, w, k, c, s, fused):
     (49, 128, 256, "pipe64x64"),          # K < 256
     (400, 96, 24, "slab64x32p2"),         # 128-pixel slabs would leave compute units idle
     (64 * 784, 96, 24, "slab128x32p2"),
-    (10192, 864, 24, "pipe64x64"),        # the slab of 32 channels does not fit
+    (64 * 784, 144, 24, "slab64x32p2"),   # K >= 128
+    (10192, 864, 24, "pipe64x64"),        # K above 512
     (12544, 512, 512, "pipe128x128"),
 ])
 def test_pointwise_default_tile(m, k, c, name):
