@@ -296,6 +296,24 @@ def mgi_plan_run(p, in_ptrs, out_ptrs, stream=None):
     _check(lib().mgi_plan_run(p, ins, outs, P(stream or 0)))
 
 
+_PTR_ARRAYS = {}
+
+
+def _ptr_array(n):
+    """The ctypes array type of n pointers (building one takes longer than a call)."""
+    t = _PTR_ARRAYS.get(n)
+    if t is None:
+        t = _PTR_ARRAYS[n] = P * max(1, n)
+    return t
+
+
+def plan_run_ptrs(p, in_ptrs, out_ptrs, stream):
+    """mgi_plan_run for a caller that has checked the pointer counts against the plan."""
+    status = _lib.mgi_plan_run(p, _ptr_array(len(in_ptrs))(*in_ptrs), _ptr_array(len(out_ptrs))(*out_ptrs), stream)
+    if status != MGI_OK:
+        _check(status)
+
+
 def mgi_plan_run_noalloc(p, in_ptrs, out_ptrs, stream=None):
     ins, outs = _io_arrays(p, in_ptrs, out_ptrs)
     _check(lib().mgi_plan_run_noalloc(p, ins, outs, P(stream or 0)))

@@ -238,6 +238,7 @@ struct PwDwParams {
 // Tiling of one configuration: images per tile (whole-image tiles) or bands
 // per image, tile groups, channel blocks per tile, LDS bytes.
 struct PwDwGeom {
+    int inst;            // kernel instance
     int ipt, nbands, groups, nbt, pstride;
     size_t lds;
     float cost;          // estimated time, us
@@ -251,7 +252,8 @@ int pwdw_best(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int ks
 // 0 <= cfg < that number, its geometry and name.
 int pwdw_configs(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int ksp, int nb16, int cfg,
                  PwDwGeom *g, const char **name);
-hipError_t launch_pwdw(const PwDwParams &p, int cfg, hipStream_t st);
+// geo: the geometry pwdw_configs gives for the parameters' shape
+hipError_t launch_pwdw(const PwDwParams &p, const PwDwGeom &geo, hipStream_t st);
 
 // MobileNet-v2 inverted residual block in one kernel: pointwise expansion
 // (+ bias, act1), depthwise 3x3 (+ bias, act2) and pointwise projection

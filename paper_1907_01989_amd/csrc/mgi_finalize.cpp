@@ -211,9 +211,10 @@ void add_pwdw_configs(Node &nd) {
                                       nd.dw_conv.pad_t, nd.dw_conv.pad_l, nd.ksp, nd.nb16, -1, nullptr, nullptr);
     for (int c = 0; c < nf; ++c) {
         const char *name = "";
-        kern::pwdw_configs(s.n, s.h, s.w, nd.dw_out.h, nd.dw_out.w, nd.dw_conv.stride_h, nd.dw_conv.pad_t,
-                           nd.dw_conv.pad_l, nd.ksp, nd.nb16, c, nullptr, &name);
         Node::Config fc{GemmTile{}, 0, name, false, c};
+        kern::pwdw_configs(s.n, s.h, s.w, nd.dw_out.h, nd.dw_out.w, nd.dw_conv.stride_h, nd.dw_conv.pad_t,
+                           nd.dw_conv.pad_l, nd.ksp, nd.nb16, c, &fc.geo, &name);
+        fc.name = name;
         nd.cfgs.push_back(fc);
     }
     // the lowest estimate first, the others in table order
@@ -269,8 +270,10 @@ void add_irb_configs(Node &nd) {
     const int nf = kern::pwdw_configs(s.n, s.h, s.w, d.h, d.w, st, pt, pl, nd.ksp, nd.nb16, -1, nullptr, nullptr);
     for (int c = 0; c < nf; ++c) {
         const char *name = "";
-        kern::pwdw_configs(s.n, s.h, s.w, d.h, d.w, st, pt, pl, nd.ksp, nd.nb16, c, nullptr, &name);
-        two.push_back(Node::Config{GemmTile{}, 0, std::string(name) + "+" + tile_name(nd.pj_tile), true, c, 1});
+        Node::Config tc{GemmTile{}, 0, "", true, c, 1};
+        kern::pwdw_configs(s.n, s.h, s.w, d.h, d.w, st, pt, pl, nd.ksp, nd.nb16, c, &tc.geo, &name);
+        tc.name = std::string(name) + "+" + tile_name(nd.pj_tile);
+        two.push_back(tc);
     }
     GemmTile t;
     pick_pipe_tile(t, s.pixels(), nd.nb16 * 16);

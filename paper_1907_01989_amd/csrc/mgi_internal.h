@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "../../include/mgi.h"
+#include "kernels.h"
 
 // Every extern "C" entry point runs its body inside MGI_ABI_TRY /
 // MGI_ABI_CATCH(name): no C++ exception crosses the C boundary; an allocation
@@ -161,6 +162,7 @@ struct Node {
     bool irb_default = false;   // Irb: the block kernel is the default configuration
     int pwdw_cfg = 0;       // PwDw / StemDw: configuration of the fused kernel (pwdw_configs,
                             // stemdw_configs)
+    kern::PwDwGeom pwdw_geo{};
     size_t cnt_off = 0;     // FcSoftmax: its row-tile arrival counters in the workspace's
                             // state region
     // Irb (a PwDw node that also runs the pointwise projection reading its
@@ -184,6 +186,7 @@ struct Node {
         bool split = false;
         int pwdw_cfg = 0;
         int mode = 0;
+        kern::PwDwGeom geo{};   // PwDw / Irb: the fused kernel's geometry
     };
     std::vector<Config> cfgs;
     int cfg = 0;
@@ -194,6 +197,7 @@ struct Node {
         split = cfgs[c].split;
         pwdw_cfg = cfgs[c].pwdw_cfg;
         mode = cfgs[c].mode;
+        pwdw_geo = cfgs[c].geo;
     }
 };
 

@@ -114,7 +114,7 @@ hipError_t launch_node_pwdw(const mgi_plan &p, const Node &nd, const Bases &B, v
     q.S = nd.dw_conv.stride_h; q.pt = nd.dw_conv.pad_t; q.pl = nd.dw_conv.pad_l;
     q.act2 = nd.dw_act;
     q.ns = ns;
-    return launch_pwdw(q, nd.pwdw_cfg, st);
+    return launch_pwdw(q, nd.pwdw_geo, st);
 }
 
 // The pointwise GEMM of a PwDw or Irb node's expansion into its scratch
@@ -277,7 +277,7 @@ hipError_t launch_pwdw_node(const mgi_plan &p, const Node &nd, const Bases &B, v
     q.S = nd.dw_conv.stride_h; q.pt = nd.dw_conv.pad_t; q.pl = nd.dw_conv.pad_l;
     q.act2 = nd.dw_act;
     q.ns = slices(os.c);
-    return launch_pwdw(q, nd.pwdw_cfg, st);
+    return launch_pwdw(q, nd.pwdw_geo, st);
 }
 
 hipError_t launch_gemmpool_node(const mgi_plan &p, const Node &nd, const Bases &B, void *y, hipStream_t st) {

@@ -529,6 +529,7 @@ int applicable(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int k
     for (int k = 0; k < kNumInsts; ++k) {
         PwDwGeom g{};
         if (!fits(kInsts[k], N, H, W, OH, OW, S, pt, pl, ksp, nb16, &g)) continue;
+        g.inst = k;
         if (idx) idx[n] = k;
         if (geo) geo[n] = g;
         ++n;
@@ -565,19 +566,19 @@ int pwdw_configs(int N, int H, int W, int OH, int OW, int S, int pt, int pl, int
     return n;
 }
 
-hipError_t launch_pwdw(const PwDwParams &p, int cfg, hipStream_t st) {
-    int idx[kNumInsts];
-    PwDwGeom geo[kNumInsts];
-    const int n = applicable(p.N, p.H, p.W, p.OH, p.OW, p.S, p.pt, p.pl, p.ksp, p.nb16, idx, geo);
-    if (cfg < 0 || cfg >= n || p.M != p.N * p.H * p.W || p.ksp % 4 != 0 || p.nb16 <= 0) return hipErrorInvalidValue;
-    const PwDwGeom &g = geo[cfg];
+hipError_t launch_pwdw(const PwDwParams &p, const PwDwGeom &geo, hipStream_t st) {
+    // (one instance's conditions again: the geometry belongs to this shape)
+    PwDwGeom g{};
+    if (geo.inst < 0 || geo.inst >= kNumInsts || p.nb16 <= 0 || p.ksp % 4 != 0 || p.M != p.N * p.H * p.W ||
+        !fits(kInsts[geo.inst], p.N, p.H, p.W, p.OH, p.OW, p.S, p.pt, p.pl, p.ksp, p.nb16, &g))
+        return hipErrorInvalidValue;
+    if (p.N <= 0) return hipSuccess;
     PwDwParams q = p;
     q.ipt = g.ipt;
     q.nbands = g.nbands;
     q.pstride = g.pstride;
     q.ntiles = (p.nb16 + g.nbt - 1) / g.nbt;
-    if (p.N <= 0) return hipSuccess;
-    return p.bf16 ? launch_inst<BF16>(idx[cfg], q, g.lds, st) : launch_inst<F16>(idx[cfg], q, g.lds, st);
+    return p.bf16 ? launch_inst<BF16>(geo.inst, q, g.lds, st) : launch_inst<F16>(geo.inst, q, g.lds, st);
 }
 
 }  // namespace kern

@@ -14,9 +14,25 @@ def _stream_handle(stream):
     """A torch stream, a raw hipStream_t (int), or None for torch's current stream."""
     if isinstance(stream, int):
         return stream
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    # (the handle without the Stream object around it: 0.3 instead of 2.9 us)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
+
+
+_TORCH_TYPES = {}
+
+
+def _torch_types():
+    """Element type code -> torch dtype (torch is imported on first use)."""
+    if not _TORCH_TYPES:
+        import torch
+        _TORCH_TYPES.update({B.DTYPE_FP16: torch.float16, B.DTYPE_FP32: torch.float32, B.DTYPE_INT32: torch.int32})
+    return _TORCH_TYPES
 
 
 def build_graph(desc):
@@ -162,15 +178,34 @@ class Plan:
                     raise ValueError(f"{role} {i}: must be a contiguous tensor of {nbytes} bytes "
                                      f"(NHWC {shape}), got {tuple(x.shape)}")
 
+    def _io_ok(self, inputs, outputs):
+        """The conditions of check_io, as quickly as Python allows (a run of
+        two kernels takes about 8 us in the library)."""
+        import torch
+        if len(inputs) != self.n_inputs or len(outputs) != self.n_outputs:
+            return False
+        dev = torch.device(self.device).index
+        if dev is None:
+            dev = torch.cuda.current_device()
+        types = _torch_types()
+        for ts, info in ((inputs, self.inputs_info), (outputs, self.outputs_info)):
+            for x, (_, dt, nbytes) in zip(ts, info):
+                if not (isinstance(x, torch.Tensor) and x.is_cuda and x.get_device() == dev and
+                        x.dtype is types[dt] and x.is_contiguous() and x.nbytes == nbytes):
+                    return False
+        return True
+
     def run(self, inputs, outputs=None, stream=None):
         """Enqueue one forward pass; returns the output tensors (not synchronised)."""
         if not self.bound:
             raise RuntimeError("plan is not bound to device memory (call bind())")
         if outputs is None:
             outputs = self.alloc_outputs()
-        self.check_io(inputs, outputs)
-        B.mgi_plan_run(self.handle, [x.data_ptr() for x in inputs],
-                       [y.data_ptr() for y in outputs], _stream_handle(stream))
+        if not (isinstance(inputs, (list, tuple)) and isinstance(outputs, (list, tuple)) and
+                self._io_ok(inputs, outputs)):
+            self.check_io(inputs, outputs)
+        B.plan_run_ptrs(self.handle, [x.data_ptr() for x in inputs], [y.data_ptr() for y in outputs],
+                        _stream_handle(stream))
         return outputs
 
     def autotune(self, inputs, outputs=None, reps=5, stream=None):
