@@ -379,7 +379,7 @@ __device__ __forceinline__ void store_tile_nhwc(const GemmParams &p, const f4 (&
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = act_apply(acc[i][j][r], p.act1);
             if (p.res && c < 8 * p.ns) {
-                const h4 rv = *((const h4 *)(p.res + (size_t)(c >> 3) * p.M + m) + ((c >> 2) & 1));
+                const h4 rv = *((const h4 *)(p.res + (size_t)(c >> 3) * p.rs + (size_t)m * p.rp) + ((c >> 2) & 1));
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = act_apply(v[r] + E::get4(rv, r), p.act2);
             }
@@ -422,7 +422,7 @@ __device__ __forceinline__ void store_tile_c8(const GemmParams &p, const f4 (&ac
         float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         const size_t off = (size_t)os * p.M + m;
         if (p.res) {
-            const h8 rv = p.res[off];
+            const h8 rv = p.res[(size_t)os * p.rs + (size_t)m * p.rp];
 #pragma unroll
             for (int r = 0; r < 8; ++r) v[r] = act_apply(v[r] + E::get(rv, r), p.act2);
         }

@@ -74,13 +74,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmParams p) {
             const int ks = kk * 4 + xsl[i];
             if (xon[i] && ks < p.ksl) {
                 if (!TAPS) {
-                    v = p.x[(size_t)ks * p.M + xm[i]];
+                    v = p.x[(size_t)ks * p.xs + (size_t)xm[i] * p.xp];
                 } else {
                     const int tap = ks / p.sin, s = ks - tap * p.sin;
                     const int ky = tap / p.kw, kx = tap - ky * p.kw;
                     const int iy = xiy[i] + ky * p.dh, ix = xix[i] + kx * p.dw;
                     if (iy >= 0 && iy < p.H && ix >= 0 && ix < p.W)
-                        v = p.x[(size_t)s * p.Min + ((size_t)xn[i] * p.H + iy) * p.W + ix];
+                        v = p.x[(size_t)s * p.xs + (((size_t)xn[i] * p.H + iy) * p.W + ix) * p.xp];
                 }
             }
             xr[i] = v;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmParams p) {
                 if (os >= p.ns) continue;
                 const size_t off = ((size_t)os * p.M + m) * 8 + hoff;
                 if (p.res) {
-                    const h4 rv = *(const h4 *)((const _Float16 *)p.res + off);
+                    const h4 rv = *(const h4 *)((const _Float16 *)(p.res + (size_t)os * p.rs + (size_t)m * p.rp) + hoff);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) v[r] = act_apply(v[r] + E::get4(rv, r), p.act2);
                 }
@@ -301,19 +301,15 @@ __global__ __launch_bounds__(256, 2) void gemm_xs_kernel(GemmParams p) {
     // last row (its results are never stored); a K slice past the end (K not
     // a multiple of 32) reads the last real slice, whose products meet the
     // zero-padded weights of those K positions (exact for finite activations).
-    int xm[FM], xmc[FM];
+    const h8 *xpx[FM];
 #pragma unroll
-    for (int j = 0; j < FM; ++j) {
-        xm[j] = m0 + j * 16 + (lane & 15);
-        xmc[j] = xm[j] < p.M ? xm[j] : p.M - 1;
-    }
+    for (int j = 0; j < FM; ++j) xpx[j] = p.x + (size_t)min(m0 + j * 16 + (lane & 15), p.M - 1) * p.xp;
     const int xsl = lane >> 4;
     h8 xq[PF][FM];
     auto xload = [&](int kk, h8 *dst) {
-        const int ks = min(kk * 4 + xsl, p.ksl - 1);
-        const h8 *src = p.x + (size_t)ks * p.M;
+        const size_t ks = (size_t)min(kk * 4 + xsl, p.ksl - 1) * p.xs;
 #pragma unroll
-        for (int j = 0; j < FM; ++j) dst[j] = src[xmc[j]];
+        for (int j = 0; j < FM; ++j) dst[j] = xpx[j][ks];
     };
 #pragma unroll
     for (int u = 0; u < PF; ++u)
@@ -485,14 +481,19 @@ __device__ __forceinline__ int div_uniform(int x, unsigned inv) {   // x, d < 32
     return (int)__umulhi((unsigned)x << 1, inv);
 }
 
-template <int BM, int BN, int KS, int TAPS>
+// XN: the input is an NHWC fp16 array (xs = 1).  A wave load is then 16 pixels of
+// four K slices, 64 consecutive bytes per pixel, and a stage holds [KS / 4]
+// groups of [BM pixels][4 slices]; the slice a lane takes is XORed with bits of
+// its pixel, so that the fragment reads (16 pixels of one slice per lane
+// group) fall on different banks.
+template <int BM, int BN, int KS, int TAPS, bool XN>
 struct PipeLoader {
     using T = PipeTile<BM, BN, KS>;
-    static constexpr int PB = BM / 64;                  // 64-pixel blocks of a tile
-    static constexpr int NS = T::XL / PB;               // K slices a wave loads per stage
+    static constexpr int PB = XN ? T::XL : BM / 64;     // loads of different pixels
+    static constexpr int NS = T::XL / PB;               // K slices a wave loads per stage (XN: groups of four)
     static_assert(T::XL % PB == 0, "a wave's loads start at the tile's first pixels");
     const GemmParams &p;
-    int wave;
+    int wave, lsl;                                      // lsl: the lane's slice of a group (XN)
     const h8 *xb;                                       // tile's first row (or image), slice 0
     uint32_t xoff[PB];                                  // lane's pixels, bytes from xb
     const h8 *wb[T::WL];                                // weights of the wave's loads, stage 0
@@ -500,6 +501,11 @@ struct PipeLoader {
     // TAPS
     uint32_t mask[PB];                                  // taps inside the input
     uint64_t at[T::XL], step[PB];                       // TAPS == 2: addresses of the current tap
+
+    // first K slice, within its stage, of the wave's load i
+    __device__ __forceinline__ int slice_of(int i) const {
+        return XN ? (wave * T::XL + i) / (BM / 16) * 4 : wave * NS + i / PB;
+    }
 
     __device__ __forceinline__ PipeLoader(const GemmParams &p_, int m0, int nb0, int wave_, int lane)
         : p(p_), wave(wave_) {
@@ -510,22 +516,21 @@ struct PipeLoader {
             wb[i] = p.w + ((size_t)min(nb0 + q, p.nb16 - 1) * p.ksp + 4 * sub) * 16;
         }
         woff = lane * 16;
-        if constexpr (TAPS == 0) {
-            xb = p.x + m0;
+        lsl = XN ? (lane & 3) ^ ((lane >> 4) & 3) : 0;
+        const int hw = TAPS ? p.OH * p.OW : 1, n0 = TAPS ? m0 / hw : 0;
+        // (TAPS: offsets from the origin of the tile's first image's first
+        // window, which keeps them non-negative)
+        if constexpr (TAPS == 0) xb = p.x + (size_t)m0 * p.xp;
+        else xb = p.x + ((int64_t)n0 * p.H * p.W - (p.pt * p.W + p.pl)) * p.xp;
 #pragma unroll
-            for (int b = 0; b < PB; ++b)                 // rows past M are never stored
-                xoff[b] = (uint32_t)min(b * 64 + lane, p.M - 1 - m0) * 16u;
-        } else {
-            const int hw = p.OH * p.OW, n0 = m0 / hw;
-            // (offsets from the origin of the tile's first image's first
-            // window, which keeps them non-negative)
-            xb = p.x + (size_t)n0 * p.H * p.W - (p.pt * p.W + p.pl);
-#pragma unroll
-            for (int b = 0; b < PB; ++b) {
-                const int m = min(m0 + b * 64 + lane, p.M - 1), n = m / hw, r = m - n * hw;
+        for (int b = 0; b < PB; ++b) {
+            const int row = XN ? (wave * T::XL + b) % (BM / 16) * 16 + (lane >> 2) : b * 64 + lane;
+            int px = min(row, p.M - 1 - m0);             // rows past M are never stored
+            if constexpr (TAPS != 0) {
+                const int m = m0 + px, n = m / hw, r = m - n * hw;
                 const int oy = r / p.OW, ox = r - oy * p.OW;
                 const int iy = oy * p.sh - p.pt, ix = ox * p.sw - p.pl;
-                xoff[b] = (uint32_t)((((n - n0) * p.H + oy * p.sh) * p.W + ox * p.sw) * 16);
+                px = ((n - n0) * p.H + oy * p.sh) * p.W + ox * p.sw;
                 uint32_t mk = 0, bit = 1;
                 for (int ky = 0; ky < p.kh; ++ky)
                     for (int kx = 0; kx < p.kw; ++kx, bit <<= 1) {
@@ -534,29 +539,37 @@ struct PipeLoader {
                     }
                 mask[b] = mk;
             }
+            xoff[b] = (uint32_t)px * (XN ? (uint32_t)p.xp : 1u) * 16u + lsl * 16u;
         }
     }
 
-    // address of the lane's pixel of block b under tap `tap`, K slice ks's
-    // input slice s (selects, not branches: an address computed under a lane
-    // condition becomes an exec-masked branch)
+    // address of the lane's pixel of block b under tap `tap`, input slice s
+    // (selects, not branches: an address computed under a lane condition
+    // becomes an exec-masked branch)
     __device__ __forceinline__ uint64_t tap_addr(int b, int tap, int s, bool &in) const {
         const int ky = div_uniform(tap, p.inv_kw), kx = tap - ky * p.kw;
-        const uint64_t base = (uint64_t)(xb + (size_t)s * p.Min + (ky * p.dh * p.W + kx * p.dw));
+        const int64_t pix = ky * p.dh * p.W + kx * p.dw;
+        const uint64_t base = (uint64_t)(xb + (XN ? s + pix * p.xp : (int64_t)s * p.xs + pix));
         in = (mask[b] & (1u << tap)) != 0;
         const uint64_t a = base + xoff[b], z = (uint64_t)p.zero;
         return ((uint64_t)(in ? (uint32_t)(a >> 32) : (uint32_t)(z >> 32)) << 32) | (in ? (uint32_t)a : (uint32_t)z);
     }
 
     // Loads of stage kk into `st`; stages are issued in order.  last: kk is
-    // the last stage (whose K slices may run past the end).
+    // the last stage (whose K slices may run past the end; they meet zero
+    // weights, and read the last real slice, or the zero element).
     __device__ __forceinline__ void issue(int kk, h8 *st, bool last) {
-        const int k0 = kk * KS + wave * NS;              // the wave's first K slice
         if constexpr (TAPS == 0) {
 #pragma unroll
             for (int i = 0; i < T::XL; ++i) {
-                const int ks = last ? min(k0 + i / PB, p.ksl - 1) : k0 + i / PB;   // K tail meets zero weights
-                load_lds16(xb + (size_t)ks * p.M, xoff[i % PB], st + (wave * T::XL + i) * 64);
+                const int ks = kk * KS + slice_of(i);
+                h8 *dst = st + (wave * T::XL + i) * 64;
+                if constexpr (XN) {
+                    const uint32_t over = last ? (uint32_t)max(0, ks + lsl - (p.ksl - 1)) * 16u : 0u;
+                    load_lds16(xb + ks, xoff[i] - over, dst);
+                } else {
+                    load_lds16(xb + (size_t)(last ? min(ks, p.ksl - 1) : ks) * p.xs, xoff[i % PB], dst);
+                }
             }
         } else if constexpr (TAPS == 2) {
             // (sin is a multiple of KS: the stage's tap, and its first slice)
@@ -565,10 +578,8 @@ struct PipeLoader {
 #pragma unroll
                 for (int i = 0; i < T::XL; ++i) {
                     bool in;
-                    at[i] = tap_addr(i % PB, tap, wave * NS + i / PB, in);
-                    if (tap * p.sin >= p.ksl) at[i] = (uint64_t)p.zero, in = false;   // stages past the end
-                    if (i < PB) step[i] = in ? (uint64_t)KS * p.Min * 16u : 0u;
-                    // (slices past a tap that reads zero: the same zero element)
+                    at[i] = tap_addr(i % PB, tap, slice_of(i), in);    // (past the last tap: no bit of the mask)
+                    if (i < PB) step[i] = in ? (uint64_t)KS * (XN ? 1 : p.xs) * 16u : 0u;
                 }
             }
 #pragma unroll
@@ -577,9 +588,10 @@ struct PipeLoader {
                 at[i] += step[i % PB];
             }
         } else {
+            static_assert(TAPS != 1 || !XN, "an NHWC input is walked a tap at a time");
 #pragma unroll
             for (int i = 0; i < T::XL; ++i) {
-                const int ks = k0 + i / PB;
+                const int ks = kk * KS + slice_of(i);
                 const int tap = div_uniform(ks, p.inv_sin);
                 bool in;
                 uint64_t a = tap_addr(i % PB, tap, ks - tap * p.sin, in);   // (past the end: no bit of the mask)
@@ -596,7 +608,7 @@ struct PipeLoader {
 // BM pixels; an M-tile then holds p.ipt whole images (rows mt * ipt * hw
 // on), and the epilogue writes the pooled means instead of the tile (see
 // pool_epilogue).  TAPS: a windowed convolution (PipeLoader).
-template <typename E, int BM, int BN, bool POOL, int KS = 4, int TAPS = 0>
+template <typename E, int BM, int BN, bool POOL, int KS = 4, int TAPS = 0, bool XN = false>
 __global__ __launch_bounds__(256, 2) void gemm_pipe_kernel(GemmParams p) {
     using T = PipeTile<BM, BN, KS>;
     constexpr int WMP = BM / 2, WNC = BN / 2, FM = WMP / 16, FN = WNC / 16;
@@ -613,7 +625,7 @@ __global__ __launch_bounds__(256, 2) void gemm_pipe_kernel(GemmParams p) {
     const int m0 = POOL ? mt * p.ipt * p.hw : mt * BM, nb0 = nt * (BN / 16);
     const int nk = p.ksp / T::KS;
 
-    PipeLoader<BM, BN, KS, TAPS> ld(p, m0, nb0, wave, lane);
+    PipeLoader<BM, BN, KS, TAPS, XN> ld(p, m0, nb0, wave, lane);
     f4 acc[FN][FM];
 #pragma unroll
     for (int i = 0; i < FN; ++i) {
@@ -635,8 +647,10 @@ __global__ __launch_bounds__(256, 2) void gemm_pipe_kernel(GemmParams p) {
 #pragma unroll
             for (int i = 0; i < FN; ++i) f.a[sub][i] = st[T::XE + ((wn * FN + i) * T::SUB + sub) * 64 + lane];
 #pragma unroll
-            for (int j = 0; j < FM; ++j)
-                f.b[sub][j] = st[(4 * sub + (lane >> 4)) * BM + wm * WMP + j * 16 + (lane & 15)];
+            for (int j = 0; j < FM; ++j) {
+                const int px = wm * WMP + j * 16 + (lane & 15), sl = lane >> 4;
+                f.b[sub][j] = XN ? st[(sub * BM + px) * 4 + (sl ^ ((px >> 2) & 3))] : st[(4 * sub + sl) * BM + px];
+            }
         }
     };
     auto mma = [&](const Frags &f) {
@@ -703,13 +717,28 @@ __global__ __launch_bounds__(256, 2) void gemm_pipe_kernel(GemmParams p) {
     store_tile_c8<E, FM, FN>(p, acc, m0 + wm * WMP, nb0 + wn * FN, (float *)stage, lane);
 }
 
-template <typename E, int BM, int BN>
+// one launch of the ring kernel, with the sliced or the NHWC loader (the latter
+// for fp16 storage, whose elements the graph input holds as they are)
+template <typename E, int BM, int BN, bool POOL, int KS, int TAPS>
+static hipError_t launch_ring(const GemmParams &q, hipStream_t st) {
+    const dim3 grid(q.mtiles * q.ntiles), block(256);
+    if (q.xp == 1) {
+        launch((gemm_pipe_kernel<E, BM, BN, POOL, KS, TAPS, false>), grid, block, 0, st, q);
+    } else if constexpr (!E::bf && TAPS != 1) {
+        if (q.xs != 1) return hipErrorInvalidValue;
+        launch((gemm_pipe_kernel<E, BM, BN, POOL, KS, TAPS, true>), grid, block, 0, st, q);
+    } else {
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <typename E, int BM, int BN, int KS = 4>
 static hipError_t launch_pipe_t(const GemmParams &p, hipStream_t st) {
     GemmParams q = p;
     q.mtiles = (p.M + BM - 1) / BM;
     q.ntiles = (p.nb16 * 16 + BN - 1) / BN;
-    launch((gemm_pipe_kernel<E, BM, BN, false>), dim3(q.mtiles * q.ntiles), dim3(256), 0, st, q);
-    return hipGetLastError();
+    return launch_ring<E, BM, BN, false, KS, 0>(q, st);
 }
 
 static unsigned inv31(int d) { return (unsigned)((0x80000000ull + d - 1) / d); }
@@ -721,6 +750,11 @@ bool conv_pipe_ok(int kh, int kw, int ksp, int H, int W, int OH, int OW) {
     return (int64_t)kh * kw <= kMaxTaps && ksp < 32768 && imgs * H * W < (1ull << 26);
 }
 
+bool conv_nhwc_ok(int sin, int ks, int H, int W, int OH, int OW) {
+    const uint64_t imgs = 128 / ((uint64_t)OH * OW) + 3;
+    return sin % ks == 0 && imgs * H * W * sin < (1ull << 27);
+}
+
 template <typename E, int BM, int BN, int KS>
 static hipError_t launch_conv_t(const GemmParams &p, hipStream_t st) {
     GemmParams q = p;
@@ -728,10 +762,9 @@ static hipError_t launch_conv_t(const GemmParams &p, hipStream_t st) {
     q.ntiles = (p.nb16 * 16 + BN - 1) / BN;
     q.inv_sin = inv31(p.sin);
     q.inv_kw = inv31(p.kw);
-    const dim3 grid(q.mtiles * q.ntiles), block(256);
-    if (p.sin % KS == 0) launch((gemm_pipe_kernel<E, BM, BN, false, KS, 2>), grid, block, 0, st, q);
-    else launch((gemm_pipe_kernel<E, BM, BN, false, KS, 1>), grid, block, 0, st, q);
-    return hipGetLastError();
+    if (p.xp != 1 && !conv_nhwc_ok(p.sin, KS, p.H, p.W, p.OH, p.OW)) return hipErrorInvalidValue;
+    if (p.sin % KS == 0) return launch_ring<E, BM, BN, false, KS, 2>(q, st);
+    return launch_ring<E, BM, BN, false, KS, 1>(q, st);
 }
 
 template <typename E>
@@ -751,14 +784,13 @@ hipError_t launch_gemm_conv(const GemmParams &p, int bm, int bn, int ks, hipStre
     return p.bf16 ? launch_conv_e<BF16>(p, bm, bn, ks, st) : launch_conv_e<F16>(p, bm, bn, ks, st);
 }
 
-template <typename E, int BM, int BN>
+template <typename E, int BM, int BN, int KS = 4>
 static hipError_t launch_pipe_pool_t(const GemmParams &p, hipStream_t st) {
     GemmParams q = p;
     q.ipt = BM / p.hw;
     q.mtiles = (p.nimg + q.ipt - 1) / q.ipt;
     q.ntiles = (p.nb16 * 16 + BN - 1) / BN;
-    launch((gemm_pipe_kernel<E, BM, BN, true>), dim3(q.mtiles * q.ntiles), dim3(256), 0, st, q);
-    return hipGetLastError();
+    return launch_ring<E, BM, BN, true, KS, 0>(q, st);
 }
 
 hipError_t launch_gemm_pool(const GemmParams &p, int bm, int bn, hipStream_t st) {
@@ -774,17 +806,7 @@ hipError_t launch_gemm_pool(const GemmParams &p, int bm, int bn, hipStream_t st)
 
 template <typename E>
 static hipError_t launch_pipe_k8_t(const GemmParams &p, bool pool, hipStream_t st) {
-    GemmParams q = p;
-    q.ntiles = (p.nb16 * 16 + 63) / 64;
-    if (pool) {
-        q.ipt = 64 / p.hw;
-        q.mtiles = (p.nimg + q.ipt - 1) / q.ipt;
-        launch((gemm_pipe_kernel<E, 64, 64, true, 8>), dim3(q.mtiles * q.ntiles), dim3(256), 0, st, q);
-    } else {
-        q.mtiles = (p.M + 63) / 64;
-        launch((gemm_pipe_kernel<E, 64, 64, false, 8>), dim3(q.mtiles * q.ntiles), dim3(256), 0, st, q);
-    }
-    return hipGetLastError();
+    return pool ? launch_pipe_pool_t<E, 64, 64, 8>(p, st) : launch_pipe_t<E, 64, 64, 8>(p, st);
 }
 
 // 64x64 tiles with 8 K slices (two MFMA K-steps) per ring stage: twice the

@@ -31,10 +31,15 @@ typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 
 // C = act2(act1(W * X + bias) + residual): MFMA GEMM over sliced activations.
 struct GemmParams {
-    const h8 *x;         // sliced input, [slices][Min] of 8 halves
+    // input: element (slice, pixel) of 8 halves at x[slice * xs + pixel * xp];
+    // sliced: xs = Min, xp = 1; an NHWC fp16 graph input read in place (fp16
+    // storage, whole slices): xs = 1, xp = its slices
+    const h8 *x;
+    int xs, xp;
     const h8 *w;         // packed weights [nb16][ksp][16][8]
     const float *bias;   // [nb16 * 16]
-    const h8 *res;       // sliced residual with the output's shape, or null
+    const h8 *res;       // residual with the output's shape, laid out as the input by rs, rp; or null
+    int rs, rp;
     void *y;             // sliced fp16 output, or fp32 (M x cout) for FC; null: yf alone is written
     float *yf;           // the output widened to an NHWC fp32 array (M x cout) as well, or null
     int yvec;            // ... whose 4-channel groups start on 16 bytes
@@ -80,7 +85,9 @@ hipError_t launch_gemm_pipe_k8(const GemmParams &p, bool pool, hipStream_t st);
 // shapes it covers (windows of at most kMaxTaps taps, offsets in range).
 constexpr int kMaxTaps = 31;
 constexpr int kConvTiles[4][3] = {{64, 64, 4}, {64, 32, 8}, {128, 32, 8}, {64, 128, 4}};
+// conv_nhwc_ok: ... and with an input of sin slices read as NHWC.
 bool conv_pipe_ok(int kh, int kw, int ksp, int H, int W, int OH, int OW);
+bool conv_nhwc_ok(int sin, int ks, int H, int W, int OH, int OW);
 hipError_t launch_gemm_conv(const GemmParams &p, int bm, int bn, int ks, hipStream_t st);
 // pointwise GEMM whose output feeds only a global average pool: M-tiles of
 // bm rows hold bm / hw whole images (hw <= 64 pixels each, M = nimg * hw),
@@ -222,7 +229,8 @@ struct DwTile {
 // whole images or a band of output rows (with the input rows they read), so
 // the depthwise step needs no data from other workgroups.
 struct PwDwParams {
-    const h8 *x;         // pointwise input, sliced [ksl][M]
+    const h8 *x;         // pointwise input: element (slice, pixel) at x[slice * xs + pixel * xp] (see GemmParams)
+    int xs, xp;
     const h8 *w;         // packed pointwise weights [nb16][ksp][16][8]
     const float *bias;   // [nb16 * 16]
     int M, ksl, ksp, nb16, act1;
@@ -293,7 +301,9 @@ hipError_t launch_add(const h8 *a, const h8 *b, h8 *y, size_t count, int act, bo
 hipError_t launch_pad(const h8 *x, h8 *y, int N, int S, int H, int W, int OH, int OW, int pt, int pl,
                       hipStream_t st);
 hipError_t launch_act(const h8 *x, h8 *y, size_t count, int act, bool bf16, hipStream_t st);
-hipError_t launch_gap(const h8 *x, h8 *y, const h8 *zero, int N, int HW, int S, bool bf16,
+// xp: elements between neighbouring pixels, 1 for a sliced input, S for an NHWC
+// fp16 graph input read in place
+hipError_t launch_gap(const h8 *x, int xp, h8 *y, const h8 *zero, int N, int HW, int S, bool bf16,
                       hipStream_t st);
 hipError_t launch_softmax(const float *z, float *y, int rows, int cols, hipStream_t st);
 

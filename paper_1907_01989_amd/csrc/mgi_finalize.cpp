@@ -1535,27 +1535,41 @@ void absorb_exports(mgi_plan &p) {
     }
 }
 
-// A graph input that only a depthwise node reads, in whole slices, is read by
-// that node's kernel (the ingest node stays in the list and launches nothing).
-// Not with materialize_all.
-void absorb_ingests(mgi_plan &p) {
-    std::vector<int> readers(p.bufs.size(), 0);
-    for (const Node &nd : p.nodes) {
-        for (int b : nd.in) readers[b]++;
-        if (nd.residual >= 0) readers[nd.residual]++;
-    }
+// A graph input in whole slices whose readers can all read the NHWC array is
+// read in place by them (the ingest node stays in the list and launches
+// nothing, in runs where it can be so).  Depthwise kernels convert what they
+// read; the others take fp16 inputs of fp16 plans, whose 16-byte elements are
+// the same in both layouts.  Not with materialize_all.
+void absorb_ingests(mgi_plan &p, const mgi_options &o) {
+    int bits = 0;
     for (Node &in : p.nodes) {
-        if (in.kind != NodeKind::Ingest || readers[in.out] != 1 || p.bufs[in.out].shape.c % 8 != 0) continue;
-        for (Node &dw : p.nodes) {
-            const mgi_conv_desc &c = dw.conv;
-            const Shape &os = p.bufs[dw.out].shape;
-            if (dw.kind != NodeKind::Depthwise || dw.in[0] != in.out ||
-                !kern::depthwise_reads_nhwc(c.kh, c.kw, c.stride_h, c.stride_w, c.dil_h, c.dil_w, os.n,
-                                            slices(os.c), os.h, os.w))
-                continue;
-            dw.direct_in = in.in[0];
-            in.absorbed = true;
+        if (in.kind != NodeKind::Ingest || p.bufs[in.out].shape.c % 8 != 0 || bits >= 64) continue;
+        const bool same = p.bufs[in.in[0]].in_dtype == MGI_DTYPE_FP16 && o.dtype == MGI_DTYPE_FP16;
+        std::vector<int> readers;
+        bool all = true;
+        for (size_t i = 0; i < p.nodes.size(); ++i) {
+            const Node &r = p.nodes[i];
+            const bool reads = std::find(r.in.begin(), r.in.end(), in.out) != r.in.end();
+            if (!reads && r.residual != in.out) continue;
+            readers.push_back((int)i);
+            const mgi_conv_desc &c = r.conv;
+            const Shape &os = p.bufs[r.out].shape;
+            switch (r.kind) {
+                case NodeKind::Depthwise:
+                    all = all && kern::depthwise_reads_nhwc(c.kh, c.kw, c.stride_h, c.stride_w, c.dil_h, c.dil_w, os.n,
+                                                            slices(os.c), os.h, os.w);
+                    break;
+                case NodeKind::Gemm:
+                case NodeKind::PwDw:
+                case NodeKind::GemmPool:
+                case NodeKind::Gap: all = all && same; break;
+                default: all = false;
+            }
         }
+        if (!all || readers.empty()) continue;
+        in.direct_readers = readers;
+        p.bufs[in.out].direct_src = in.in[0];
+        p.bufs[in.out].direct_bit = bits++;
     }
 }
 
@@ -1580,7 +1594,7 @@ mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p
     if (o.fuse && o.fuse_dwpw) fuse_dw_into_pw(p);
     if (o.fuse && !o.materialize_all) {
         absorb_exports(p);
-        absorb_ingests(p);
+        absorb_ingests(p, o);
     }
     for (Node &nd : p.nodes) add_configs(p, nd, p.bufs[nd.out].shape.pixels());
     compute_lifetimes(p);

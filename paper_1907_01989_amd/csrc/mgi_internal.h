@@ -89,6 +89,9 @@ struct Buf {
     int last_use = -1;       // last node index that reads it (-1: none)
     int graph_tensor = -1;   // graph tensor id it holds (-1: internal)
     bool dead = false;       // no longer produced or read (fused away); not planned
+    // a converted graph input that its readers may read in place: the input's
+    // buffer, and its bit in a run's mask of inputs read in place
+    int direct_src = -1, direct_bit = -1;
     int in_dtype = MGI_DTYPE_FP32;  // element type of a NHWC_IN buffer
 };
 
@@ -124,11 +127,12 @@ struct Node {
     // sliced output (no: it is not stored)
     int direct_out = -1;
     bool sliced_read = true;
-    // Depthwise: the graph input (buffer id) that this node's kernel reads
-    // itself, -1 = none
-    int direct_in = -1;
-    // Export and Ingest: absorbed by their neighbour that way
+    // Export: absorbed that way
     bool absorbed = false;
+    // Ingest: the nodes that read its output, all of which can read the graph
+    // input itself (in some configuration); the bit of the run's mask that says
+    // whether they do
+    std::vector<int> direct_readers;
     int act1 = MGI_ACT_NONE, act2 = MGI_ACT_NONE;
     // weights in the packed blob
     size_t w_off = 0, w_bytes = 0, b_off = 0, b_bytes = 0;

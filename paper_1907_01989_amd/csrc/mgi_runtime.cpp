@@ -32,6 +32,7 @@ struct Bases {
     const void *const *ins;
     void *const *outs;
     bool direct = false;   // kernels may read graph inputs and write graph outputs in place
+    uint64_t in_place = 0; // the inputs that they do read in place (inputs_in_place)
 };
 
 // Whether no output buffer of a run shares bytes with an input buffer (a
@@ -56,13 +57,51 @@ void *buf_ptr(const mgi_plan &p, int b, const Bases &B) {
     return nullptr;
 }
 
-// The graph input `b` for a kernel that reads it in place in 16-byte pieces,
-// or null where this run has to convert it first (the buffers overlap, or the
-// caller's array is not aligned).
-const void *direct_input(const mgi_plan &p, int b, const Bases &B) {
-    if (b < 0 || !B.direct) return nullptr;
-    const void *x = buf_ptr(p, b, B);
-    return ((uintptr_t)x & 15) ? nullptr : x;
+// Whether node nd, in its configuration, can read an input in place (a window
+// GEMM's ring walks whole taps per stage; every other kernel of the kinds
+// absorb_ingests lists can).
+bool reads_in_place(const mgi_plan &p, const Node &nd) {
+    if (nd.kind != NodeKind::Gemm || !nd.taps || !nd.tile.pipe) return true;
+    const Shape &x = p.bufs[nd.in[0]].shape, &y = p.bufs[nd.out].shape;
+    return conv_nhwc_ok((x.c + 7) / 8, nd.tile.ks, x.h, x.w, y.h, y.w);
+}
+
+// The graph inputs that a run's kernels read in place, one bit per absorbed
+// ingest node: none where outputs overlap inputs, and not an array off a
+// 16-byte boundary.
+uint64_t inputs_in_place(const mgi_plan &p, const Bases &B) {
+    uint64_t mask = 0;
+    if (!B.direct) return mask;
+    for (const Node &nd : p.nodes) {
+        if (nd.direct_readers.empty()) continue;
+        bool ok = ((uintptr_t)buf_ptr(p, nd.in[0], B) & 15) == 0;
+        for (int r : nd.direct_readers) ok = ok && reads_in_place(p, p.nodes[r]);
+        if (ok) mask |= 1ull << p.bufs[nd.out].direct_bit;
+    }
+    return mask;
+}
+
+// A sliced operand: where it is, and the distances between its slices and
+// pixels (in place: the NHWC array)
+struct Operand {
+    const h8 *x = nullptr;
+    int s = 0, p = 1;
+    bool in_place = false;
+};
+Operand operand(const mgi_plan &p, int b, const Bases &B) {
+    Operand o;
+    if (b < 0) return o;
+    const Buf &f = p.bufs[b];
+    if (f.direct_bit >= 0 && (B.in_place >> f.direct_bit & 1)) {
+        o.x = (const h8 *)buf_ptr(p, f.direct_src, B);
+        o.s = 1;
+        o.p = (f.shape.c + 7) / 8;
+        o.in_place = true;
+    } else {
+        o.x = (const h8 *)buf_ptr(p, b, B);
+        o.s = (int)f.shape.pixels();
+    }
+    return o;
 }
 
 inline int slices(int c) { return (c + 7) / 8; }
@@ -102,7 +141,8 @@ hipError_t launch_node_pwdw(const mgi_plan &p, const Node &nd, const Bases &B, v
     const char *wbase = static_cast<const char *>(p.dev_w);
     PwDwParams q{};
     q.bf16 = bf;
-    q.x = (const h8 *)buf_ptr(p, nd.in[0], B);
+    const Operand x = operand(p, nd.in[0], B);
+    q.x = x.x; q.xs = x.s; q.xp = x.p;
     q.w = (const h8 *)(wbase + nd.w_off);
     q.bias = (const float *)(wbase + nd.b_off);
     q.M = (int)nd.dw_in.pixels();
@@ -124,7 +164,8 @@ hipError_t launch_node_expand(const mgi_plan &p, const Node &nd, const Bases &B,
     const Shape mid = nd.dw_in;
     GemmParams g{};
     g.bf16 = bf;
-    g.x = (const h8 *)buf_ptr(p, nd.in[0], B);
+    const Operand x = operand(p, nd.in[0], B);
+    g.x = x.x; g.xs = x.s; g.xp = x.p;
     g.w = (const h8 *)(wbase + nd.w_off);
     g.bias = (const float *)(wbase + nd.b_off);
     g.y = buf_ptr(p, nd.scratch, B);
@@ -218,9 +259,11 @@ hipError_t launch_irb_node(const mgi_plan &p, const Node &nd, const Bases &B, vo
         GemmParams g{};
         g.bf16 = bf;
         g.x = (const h8 *)d2;
+        g.xs = (int)os.pixels(); g.xp = 1;
         g.w = (const h8 *)(wbase + nd.pj_w_off);
         g.bias = (const float *)(wbase + nd.pj_b_off);
         g.res = nd.residual >= 0 ? (const h8 *)buf_ptr(p, nd.residual, B) : nullptr;
+        g.rs = (int)os.pixels(); g.rp = 1;
         g.y = y;
         g.M = g.Min = (int)os.pixels();
         g.ksl = nd.pj_ksl; g.ksp = nd.pj_ksp;
@@ -246,7 +289,8 @@ hipError_t launch_pwdw_node(const mgi_plan &p, const Node &nd, const Bases &B, v
         void *sp = buf_ptr(p, nd.scratch, B);
         GemmParams g{};
         g.bf16 = bf;
-        g.x = (const h8 *)buf_ptr(p, nd.in[0], B);
+        const Operand x = operand(p, nd.in[0], B);
+        g.x = x.x; g.xs = x.s; g.xp = x.p;
         g.w = (const h8 *)(wbase + nd.w_off);
         g.bias = (const float *)(wbase + nd.b_off);
         g.y = sp;
@@ -265,7 +309,8 @@ hipError_t launch_pwdw_node(const mgi_plan &p, const Node &nd, const Bases &B, v
     }
     PwDwParams q{};
     q.bf16 = bf;
-    q.x = (const h8 *)buf_ptr(p, nd.in[0], B);
+    const Operand x = operand(p, nd.in[0], B);
+    q.x = x.x; q.xs = x.s; q.xp = x.p;
     q.w = (const h8 *)(wbase + nd.w_off);
     q.bias = (const float *)(wbase + nd.b_off);
     q.M = (int)nd.dw_in.pixels();
@@ -288,7 +333,8 @@ hipError_t launch_gemmpool_node(const mgi_plan &p, const Node &nd, const Bases &
     const Shape mid = nd.dw_in;
     GemmParams g{};
     g.bf16 = bf;
-    g.x = (const h8 *)buf_ptr(p, nd.in[0], B);
+    const Operand x = operand(p, nd.in[0], B);
+    g.x = x.x; g.xs = x.s; g.xp = x.p;
     g.w = (const h8 *)(wbase + nd.w_off);
     g.bias = (const float *)(wbase + nd.b_off);
     g.M = g.Min = (int)mid.pixels();
@@ -312,7 +358,7 @@ hipError_t launch_gemmpool_node(const mgi_plan &p, const Node &nd, const Bases &
     ev.start = nullptr;
     ev.stop = saved.stop;
     if (e == hipSuccess)
-        e = launch_gap((const h8 *)sp, (h8 *)y, (const h8 *)(wbase + p.zero_off), mid.n, mid.h * mid.w,
+        e = launch_gap((const h8 *)sp, 1, (h8 *)y, (const h8 *)(wbase + p.zero_off), mid.n, mid.h * mid.w,
                        slices(mid.c), bf, st);
     ev = saved;
     return e;
@@ -383,6 +429,7 @@ hipError_t launch_dwpw_node(const mgi_plan &p, const Node &nd, const Bases &B, v
     g.w = (const h8 *)(wbase + nd.w_off);
     g.bias = (const float *)(wbase + nd.b_off);
     g.res = nd.residual >= 0 ? (const h8 *)buf_ptr(p, nd.residual, B) : nullptr;
+    g.rs = (int)os.pixels(); g.rp = 1;
     g.y = y;
     g.M = (int)os.pixels();
     g.Min = g.M;
@@ -413,7 +460,7 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
     const bool bf = p.opt.dtype == MGI_DTYPE_BF16;
     switch (nd.kind) {
         case NodeKind::Ingest: {
-            if (nd.absorbed && direct_input(p, nd.in[0], B)) return mark_events(st);
+            if (operand(p, nd.out, B).in_place) return mark_events(st);
             const Buf &ib = p.bufs[nd.in[0]];
             return launch_ingest(buf_ptr(p, nd.in[0], B), ib.in_dtype == MGI_DTYPE_FP16, (h8 *)y,
                                  (int)ib.shape.pixels(), ib.shape.c, bf, st);
@@ -444,10 +491,11 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
             const Buf &ib = p.bufs[nd.in[0]];
             GemmParams q{};
             q.bf16 = bf;
-            q.x = (const h8 *)buf_ptr(p, nd.in[0], B);
+            const Operand x = operand(p, nd.in[0], B), res = operand(p, nd.residual, B);
+            q.x = x.x; q.xs = x.s; q.xp = x.p;
             q.w = (const h8 *)(wbase + nd.w_off);
             q.bias = (const float *)(wbase + nd.b_off);
-            q.res = nd.residual >= 0 ? (const h8 *)buf_ptr(p, nd.residual, B) : nullptr;
+            q.res = res.x; q.rs = res.s; q.rp = res.p;
             q.y = y;
             if (B.direct && nd.direct_out >= 0) {
                 q.yf = (float *)buf_ptr(p, nd.direct_out, B);
@@ -487,7 +535,13 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
             const Buf &ib = p.bufs[nd.in[0]];
             DwParams q{};
             q.bf16 = bf;
-            q.x = (const h8 *)buf_ptr(p, nd.in[0], B);
+            const Operand x = operand(p, nd.in[0], B);
+            if (x.in_place) {
+                q.xin = x.x;
+                q.xin_fp16 = p.bufs[p.bufs[nd.in[0]].direct_src].in_dtype == MGI_DTYPE_FP16;
+            } else {
+                q.x = x.x;
+            }
             q.w = (const h8 *)(wbase + nd.w_off);
             q.bias = (const float *)(wbase + nd.b_off);
             q.zero = (const h8 *)(wbase + p.zero_off);
@@ -498,8 +552,6 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
             q.dh = nd.conv.dil_h; q.dw = nd.conv.dil_w;
             q.pt = nd.conv.pad_t; q.pl = nd.conv.pad_l;
             q.act = nd.act1;
-            q.xin = direct_input(p, nd.direct_in, B);
-            q.xin_fp16 = q.xin && p.bufs[nd.direct_in].in_dtype == MGI_DTYPE_FP16;
             return launch_depthwise(q, nd.dw_rows, st);
         }
         case NodeKind::Add:
@@ -510,7 +562,8 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
                               (size_t)slices(os.c) * os.pixels(), nd.act1, bf, st);
         case NodeKind::Gap: {
             const Buf &ib = p.bufs[nd.in[0]];
-            return launch_gap((const h8 *)buf_ptr(p, nd.in[0], B), (h8 *)y,
+            const Operand x = operand(p, nd.in[0], B);
+            return launch_gap(x.x, x.p, (h8 *)y,
                               (const h8 *)(wbase + p.zero_off), ib.shape.n,
                               ib.shape.h * ib.shape.w, slices(ib.shape.c), bf, st);
         }
@@ -639,6 +692,7 @@ mgi_status run_plan(mgi_plan *p, const void *const *dev_inputs, void *const *dev
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!ws) ws = static_cast<char *>(p->dev_ws);
     Bases B{ws, dev_inputs, dev_outputs, io_disjoint(*p, dev_inputs, dev_outputs)};
+    B.in_place = inputs_in_place(*p, B);
     LaunchEvents &ev = launch_events();
     for (size_t i = 0; i < p->nodes.size(); ++i) {
         ev.start = start_ev ? static_cast<hipEvent_t>(start_ev[i]) : nullptr;
@@ -820,6 +874,7 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
         return hip_fail(e, "mgi_plan_autotune: events");
     }
     Bases B{static_cast<char *>(p->dev_ws), dev_inputs, dev_outputs, io_disjoint(*p, dev_inputs, dev_outputs)};
+    B.in_place = inputs_in_place(*p, B);
     LaunchEvents &ev = launch_events();
     mgi_status result = MGI_OK;
     std::vector<float> times;
@@ -830,6 +885,7 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
         float best_ms = 3.0e38f;
         for (size_t c = 0; c < nd.cfgs.size() && result == MGI_OK; ++c) {
             nd.apply((int)c);
+            B.in_place = inputs_in_place(*p, B);
             bool usable = true;
             for (int r = 0; r <= reps && usable && result == MGI_OK; ++r) {
                 // the whole plan runs, so that the node meets its input as it
@@ -878,6 +934,7 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
             }
         }
         nd.apply(best);
+        B.in_place = inputs_in_place(*p, B);
     }
     destroy();
     return result;

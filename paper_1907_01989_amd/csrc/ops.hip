@@ -504,10 +504,12 @@ hipError_t launch_zero_words(unsigned *dst, size_t words, hipStream_t st) {
 // is the sliced (n, 1, 1, c) tensor in the storage type.
 // ---------------------------------------------------------------------------
 template <typename E>
-__global__ __launch_bounds__(256) void gap_kernel(const h8 *x, h8 *y, const h8 *zero, int HW) {
+__global__ __launch_bounds__(256) void gap_kernel(const h8 *x, int xp, h8 *y, const h8 *zero, int HW, int N) {
     __shared__ float part[4][8];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const h8 *xin = x + (size_t)blockIdx.x * HW;
+    // plane b = slice * N + image; NHWC (xp = slices): pixels xp elements apart
+    const int b = blockIdx.x, sl = b / N;
+    const h8 *xin = xp == 1 ? x + (size_t)b * HW : x + (size_t)(b - sl * N) * HW * xp + sl;
     float acc[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] = 0.0f;
@@ -516,7 +518,7 @@ __global__ __launch_bounds__(256) void gap_kernel(const h8 *x, h8 *y, const h8 *
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int px = p0 + u * 256 + tid;
-            v[u] = *(px < HW ? xin + px : zero);
+            v[u] = *(px < HW ? xin + (size_t)px * xp : zero);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -545,17 +547,18 @@ __global__ __launch_bounds__(256) void gap_kernel(const h8 *x, h8 *y, const h8 *
 // the zero element instead of branching), then a 3-step butterfly inside the
 // 8-lane group.  Fixed order, so deterministic.
 template <typename E>
-__global__ __launch_bounds__(256) void gap_small_kernel(const h8 *x, h8 *y, const h8 *zero,
-                                                        int planes, int HW) {
+__global__ __launch_bounds__(256) void gap_small_kernel(const h8 *x, int xp, h8 *y, const h8 *zero,
+                                                        int planes, int HW, int N) {
     const int t = blockIdx.x * 256 + threadIdx.x;
     const int idx = t >> 3, j = t & 7;
     const bool live = idx < planes;
-    const h8 *xin = x + (size_t)(live ? idx : 0) * HW;
+    const int b = live ? idx : 0, sl = b / N;
+    const h8 *xin = xp == 1 ? x + (size_t)b * HW : x + (size_t)(b - sl * N) * HW * xp + sl;
     h8 v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int px = j + 8 * i;
-        v[i] = *((live && px < HW) ? xin + px : zero);
+        v[i] = *((live && px < HW) ? xin + (size_t)px * xp : zero);
     }
     float acc[8];
 #pragma unroll
@@ -577,20 +580,20 @@ __global__ __launch_bounds__(256) void gap_small_kernel(const h8 *x, h8 *y, cons
     }
 }
 
-hipError_t launch_gap(const h8 *x, h8 *y, const h8 *zero, int N, int HW, int S, bool bf16,
+hipError_t launch_gap(const h8 *x, int xp, h8 *y, const h8 *zero, int N, int HW, int S, bool bf16,
                       hipStream_t st) {
     const size_t planes = (size_t)S * N;
     if (!planes) return hipSuccess;
     if (HW <= 64) {
         if (bf16)
-            launch(gap_small_kernel<BF16>, dim3(blocks_for(planes * 8, 256)), dim3(256), 0, st, x, y, zero,
-                   (int)planes, HW);
+            launch(gap_small_kernel<BF16>, dim3(blocks_for(planes * 8, 256)), dim3(256), 0, st, x, xp, y, zero,
+                   (int)planes, HW, N);
         else
-            launch(gap_small_kernel<F16>, dim3(blocks_for(planes * 8, 256)), dim3(256), 0, st, x, y, zero,
-                   (int)planes, HW);
+            launch(gap_small_kernel<F16>, dim3(blocks_for(planes * 8, 256)), dim3(256), 0, st, x, xp, y, zero,
+                   (int)planes, HW, N);
     } else {
-        if (bf16) launch(gap_kernel<BF16>, dim3((unsigned)planes), dim3(256), 0, st, x, y, zero, HW);
-        else launch(gap_kernel<F16>, dim3((unsigned)planes), dim3(256), 0, st, x, y, zero, HW);
+        if (bf16) launch(gap_kernel<BF16>, dim3((unsigned)planes), dim3(256), 0, st, x, xp, y, zero, HW, N);
+        else launch(gap_kernel<F16>, dim3((unsigned)planes), dim3(256), 0, st, x, xp, y, zero, HW, N);
     }
     return hipGetLastError();
 }

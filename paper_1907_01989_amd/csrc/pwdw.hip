@@ -130,13 +130,13 @@ __global__ __launch_bounds__(NW * 64, 2) void pwdw_kernel(PwDwParams p) {   // >
     // condition the compiler can count the loads in flight and wait only for
     // the one a step consumes, so the loads for the next PF-1 steps stay in
     // flight.  Otherwise the slots take all of K at once, each step once.
-    int mj[FMW];
+    uint32_t mj[FMW];                             // element offset of the lane's pixels
     bool fj[FMW];
 #pragma unroll
     for (int j = 0; j < FMW; ++j) {
         const int f = wave + j * NW;
         fj[j] = f * 16 < P;
-        mj[j] = m0 + min(f * 16 + (lane & 15), P - 1);
+        mj[j] = (m0 + min(f * 16 + (lane & 15), P - 1)) * p.xp;
     }
     const int xsl = lane >> 4;
     h8 xq[PF][FMW];
@@ -144,9 +144,9 @@ __global__ __launch_bounds__(NW * 64, 2) void pwdw_kernel(PwDwParams p) {   // >
     // kernel only for inputs of at most 4 GiB)
     auto xload = [&](int kk, h8 *dst) {
         const uint32_t ks = min(kk * 4 + xsl, p.ksl - 1);   // K tail meets zero weights
-        const uint32_t off = ks * (uint32_t)p.M;
+        const uint32_t off = ks * (uint32_t)p.xs;
 #pragma unroll
-        for (int j = 0; j < FMW; ++j) dst[j] = *(const h8 *)((const char *)p.x + (off + (uint32_t)mj[j]) * 16u);
+        for (int j = 0; j < FMW; ++j) dst[j] = *(const h8 *)((const char *)p.x + (off + mj[j]) * 16u);
     };
     if constexpr (DEEP) {
 #pragma unroll

@@ -116,3 +116,60 @@ def test_output_in_the_input_buffer():
         plan.run([xi], [yo])
         torch.cuda.synchronize()
         np.testing.assert_array_equal(yo.cpu().numpy(), want)
+
+
+def _inplace_net(kind, n, h, w, c, cout):
+    g = NetBuilder(seed=c + cout)
+    x = g.input(n, h, w, c, -1, 1, dtype=workloads.DTYPE_FP16)
+    if kind == "pw":
+        y = [g.conv(x, cout, 1)]
+    elif kind == "block":                       # expansion, depthwise, projection, residual from the input
+        t = g.conv(g.dw(g.conv(x, cout, 1), 3), c, 1, act=ACT_NONE)
+        y = [g.add(t, x)]
+    elif kind == "down":
+        y = [g.dw(g.conv(x, cout, 1), 3, 2)]
+    elif kind == "pool":
+        y = [g.gap(g.conv(x, cout, 1))]
+    elif kind == "conv":
+        y = [g.conv(x, cout, 3)]
+    else:                                       # two readers, one of them the pool
+        y = [g.conv(x, cout, 1), g.gap(x), g.dw(x, 3)]
+    for t in y:
+        g.mark_output(t)
+    return g.graph(kind)
+
+
+@pytest.mark.parametrize("kind,n,h,w,c,cout", [
+    ("pw", 1, 1, 1, 8, 16), ("pw", 3, 9, 7, 40, 72), ("pw", 2, 13, 13, 264, 136), ("pw", 1, 30, 30, 512, 40),
+    ("pw", 37, 14, 14, 96, 520),
+    ("block", 2, 14, 14, 24, 96), ("block", 1, 7, 7, 160, 320), ("block", 3, 29, 27, 32, 48),
+    ("down", 2, 15, 15, 96, 192), ("down", 1, 28, 28, 40, 64),
+    ("pool", 5, 7, 7, 320, 136), ("pool", 70, 3, 3, 72, 64), ("pool", 33, 7, 7, 512, 512),
+    ("conv", 2, 12, 11, 32, 40), ("conv", 1, 9, 9, 64, 136), ("conv", 3, 5, 5, 24, 16),
+    ("two", 2, 11, 10, 48, 24), ("two", 9, 7, 7, 16, 64),
+])
+def test_kernels_read_the_input_in_place(kind, n, h, w, c, cout):
+    """Every configuration of every node that can read an NHWC fp16 input,
+    against a plan that keeps the converted tensor; and an input off a 16-byte
+    boundary, which is converted first."""
+    import torch
+    from paper_1907_01989_amd import engine, _binding as B
+    desc = _inplace_net(kind, n, h, w, c, cout)
+    ref_plan = engine.Plan(desc, materialize_all=True, fuse_pwdw=2, fuse_pool=2)
+    x = ref_plan.input_tensors()[0]
+    ref = ref_plan.run([x])
+    plan = engine.Plan(desc, fuse_pwdw=2, fuse_pool=2)
+    for i, (m, (_, ncfg, _)) in enumerate(zip(plan.nodes(), plan.node_configs())):
+        for cfg in range(ncfg if ncfg > 1 or i == 0 else 0):
+            B.mgi_plan_set_node_config(plan.handle, i, cfg)
+            log(f"[case] in place {kind} {n}x{h}x{w}x{c}->{cout} node {i} {m['kind']} {plan.node_configs()[i][2]}")
+            for off in (0, 1):
+                xb = torch.empty(x.numel() + off, dtype=x.dtype, device=x.device)
+                xo = xb[off:].view(x.shape)
+                xo.copy_(x)
+                outs = [torch.full_like(o, 9.0) for o in ref]
+                plan.run([xo], outs)
+                torch.cuda.synchronize()
+                for o, r in zip(outs, ref):
+                    np.testing.assert_array_equal(o.cpu().numpy(), r.cpu().numpy())
+        B.mgi_plan_set_node_config(plan.handle, i, 0)
