@@ -1351,6 +1351,14 @@ void compute_lifetimes(mgi_plan &p) {
         if (nd.scratch >= 0) p.bufs[nd.scratch].producer = p.bufs[nd.scratch].last_use = (int)i;
         if (nd.scratch2 >= 0) p.bufs[nd.scratch2].producer = p.bufs[nd.scratch2].last_use = (int)i;
     }
+    // a tensor with views lives from its first view's producer to the last
+    // reader of any of them
+    for (const Buf &v : p.bufs) {
+        if (v.view_of < 0) continue;
+        Buf &b = p.bufs[v.view_of];
+        b.producer = std::min(b.producer, v.producer);
+        b.last_use = std::max(b.last_use, v.last_use);
+    }
 
 }
 
@@ -1361,7 +1369,7 @@ void plan_memory(mgi_plan &p, const mgi_options &o) {
     std::vector<size_t> sizes;
     std::vector<int> first, last;
     for (size_t b = 0; b < p.bufs.size(); ++b) {
-        if (p.bufs[b].loc != Loc::Arena || p.bufs[b].dead) continue;
+        if (p.bufs[b].loc != Loc::Arena || p.bufs[b].dead || p.bufs[b].view_of >= 0) continue;
         arena.push_back((int)b);
         sizes.push_back(p.bufs[b].bytes);
         first.push_back(p.bufs[b].producer);
@@ -1384,6 +1392,9 @@ void plan_memory(mgi_plan &p, const mgi_options &o) {
     }
     p.n_objects = (int)pr.object_size.size();
     for (size_t i = 0; i < arena.size(); ++i) p.bufs[arena[i]].offset = obj_off[pr.object_of[i]];
+    for (Buf &v : p.bufs)
+        if (v.view_of >= 0)
+            v.offset = p.bufs[v.view_of].offset + (size_t)v.view_slice * v.shape.pixels() * 16;
     // state region: arrival counters of fused FC -> softmax nodes, one per
     // tile of 16 rows (the finest row tiling of the FC kernel)
     p.state_off = off;
@@ -1535,6 +1546,37 @@ void absorb_exports(mgi_plan &p) {
     }
 }
 
+// Concatenation without a copy: slices are the slowest index of a sliced
+// tensor, so an operand in whole slices is a contiguous part of the
+// concatenated tensor, and its producer can write it there (the concat node
+// stays in the list and launches nothing).  Where every operand but the last
+// is in whole slices, and each is an intermediate tensor of its own.  Not with
+// materialize_all.
+void alias_concats(mgi_plan &p) {
+    std::vector<int> producer(p.bufs.size(), -1);
+    for (size_t i = 0; i < p.nodes.size(); ++i) producer[p.nodes[i].out] = (int)i;
+    std::vector<char> parent(p.bufs.size(), 0);
+    for (Node &cc : p.nodes) {
+        if (cc.kind != NodeKind::Concat || p.bufs[cc.out].loc != Loc::Arena || p.bufs[cc.out].view_of >= 0) continue;
+        bool ok = true;
+        for (size_t k = 0; k < cc.in.size(); ++k) {
+            const Buf &b = p.bufs[cc.in[k]];
+            ok = ok && b.layout == Layout::C8 && b.loc == Loc::Arena && !b.dead && b.view_of < 0 && !parent[cc.in[k]] &&
+                 producer[cc.in[k]] >= 0 && (b.shape.c % 8 == 0 || k + 1 == cc.in.size()) &&
+                 std::count(cc.in.begin(), cc.in.end(), cc.in[k]) == 1;
+        }
+        if (!ok) continue;
+        int slice = 0;
+        for (int b : cc.in) {
+            p.bufs[b].view_of = cc.out;
+            p.bufs[b].view_slice = slice;
+            slice += slices(p.bufs[b].shape.c);
+        }
+        parent[cc.out] = 1;
+        cc.absorbed = true;
+    }
+}
+
 // A graph input in whole slices whose readers can all read the NHWC array is
 // read in place by them (the ingest node stays in the list and launches
 // nothing, in runs where it can be so).  Depthwise kernels convert what they
@@ -1593,6 +1635,7 @@ mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p
     if (o.fuse && o.fuse_softmax) fuse_softmax_into_fc(p);
     if (o.fuse && o.fuse_dwpw) fuse_dw_into_pw(p);
     if (o.fuse && !o.materialize_all) {
+        alias_concats(p);
         absorb_exports(p);
         absorb_ingests(p, o);
     }

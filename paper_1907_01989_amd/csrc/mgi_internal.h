@@ -89,6 +89,9 @@ struct Buf {
     int last_use = -1;       // last node index that reads it (-1: none)
     int graph_tensor = -1;   // graph tensor id it holds (-1: internal)
     bool dead = false;       // no longer produced or read (fused away); not planned
+    // an operand of a concatenation that is written where the concatenated
+    // tensor has it: that tensor's buffer, and the operand's first slice there
+    int view_of = -1, view_slice = 0;
     // a converted graph input that its readers may read in place: the input's
     // buffer, and its bit in a run's mask of inputs read in place
     int direct_src = -1, direct_bit = -1;
@@ -127,7 +130,7 @@ struct Node {
     // sliced output (no: it is not stored)
     int direct_out = -1;
     bool sliced_read = true;
-    // Export: absorbed that way
+    // Export: absorbed that way; Concat: its operands are views of its output
     bool absorbed = false;
     // Ingest: the nodes that read its output, all of which can read the graph
     // input itself (in some configuration); the bit of the run's mask that says

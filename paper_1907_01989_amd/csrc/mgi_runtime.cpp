@@ -577,6 +577,7 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
                               nd.conv.pad_l, st);
         }
         case NodeKind::Concat: {
+            if (nd.absorbed) return mark_events(st);
             ConcatParams q{};
             q.nin = (int)nd.in.size();
             int off = 0;

@@ -377,3 +377,53 @@ def test_depthwise_reads_the_graph_input(n, h, w, c, k, s, d, src, dtype):
             out = plan.run([xo])[0]
             torch.cuda.synchronize()
             np.testing.assert_array_equal(out.cpu().numpy(), kept[0], err_msg=f"config {cfg} offset {off}")
+
+
+@pytest.mark.parametrize("n,h,w,c,oh,ow,align", [
+    (1, 9, 11, 5, 70, 90, True),          # one row per thread
+    (2, 13, 9, 21, 390, 345, True),       # two, an even number of rows
+    (3, 12, 20, 9, 431, 421, False),      # four, a remainder; rows that share no source row at the end
+    (1, 700, 30, 8, 701, 760, True),      # hardly any upsampling: no two rows share a source row
+])
+def test_resize_argmax_rows(n, h, w, c, oh, ow, align):
+    g = NetBuilder(seed=n + c)
+    x = sliced(g, g.input(n, h, w, c, -1, 1))
+    up = g.resize(x, oh, ow, align)
+    y = g.argmax(up)
+    g.mark_output(y)
+    desc = g.graph("resize_argmax")
+    log(f"[case] resize_argmax {n}x{h}x{w}x{c} -> {oh}x{ow}")
+    _, outs, _ = run_gpu(desc)
+    ref = oracle.run_graph(desc)
+    # exact fp16 inputs: the interpolation differs from float64 by a few fp32
+    # roundings of values up to 1, and by the coordinate's rounding (at most
+    # 2^-24 * h, on slopes of at most 2)
+    bad, covered, _ = labels_check(outs[0], ref[up], margin=1e-3)
+    assert bad == 0 and covered > 0.9
+
+
+@pytest.mark.parametrize("chans", [(16, 24, 13), (8, 8), (40, 5)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_concat_operands_written_in_place(chans, dtype):
+    """Operands whose producers write them into the concatenated tensor, one
+    of them read elsewhere too (also after the concatenation), against a plan
+    that keeps and copies every tensor; and operands that cannot be (a ragged
+    one in the middle, one used twice)."""
+    from paper_1907_01989_amd import engine
+    g = NetBuilder(seed=sum(chans))
+    x = g.input(2, 9, 7, 24, -1, 1)
+    parts = [g.conv(x, c, 1 + 2 * (i % 2)) for i, c in enumerate(chans)]
+    parts[0] = g.dw(parts[0], 3)
+    cat = g.concat(parts)
+    z = g.conv(cat, 40, 1)
+    late = g.conv(g.add(parts[0], g.conv(z, chans[0], 1)), 16, 1)
+    odd = g.concat([g.conv(z, 13, 1), late, late])
+    for t in (z, late, parts[-1], odd):
+        g.mark_output(t)
+    desc = g.graph(f"concat_{chans}")
+    log(f"[case] {desc['name']} dtype {dtype}")
+    _, kept, _ = run_gpu(desc, materialize_all=True, dtype=dtype)
+    for planner in (0, 1, 2):
+        _, outs, _ = run_gpu(desc, materialize_all=False, dtype=dtype, planner=planner)
+        for o, k in zip(outs, kept):
+            np.testing.assert_array_equal(o, k)
