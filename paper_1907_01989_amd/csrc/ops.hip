@@ -686,44 +686,75 @@ __global__ __launch_bounds__(256) void resize_kernel(ResizeParams p) {
     ((h8 *)p.y)[i] = E::pack(o);
 }
 
-template <typename E>
-__global__ __launch_bounds__(256) void resize_argmax_kernel(ResizeParams p) {
+// A thread owns U consecutive rows of an output column.  Bound by vector
+// issue: per output and class four operations blend the columns of the two
+// source rows, two blend the rows and three keep the maximum, besides widening
+// the four source values.  When upsampling, neighbouring rows mostly fall
+// between the same two source rows and share all but the last five (21
+// classes, 8 x 41 x 41 -> 641 x 641: one row per thread 28.0 us, four 23.6).
+template <typename E, int U>
+__global__ __launch_bounds__(256) void resize_argmax_kernel(ResizeParams p, int groups) {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t opix = (size_t)p.N * p.OH * p.OW;
-    if (i >= opix) return;
-    const int n = (int)(i / ((size_t)p.OH * p.OW));
-    const int q = (int)(i - (size_t)n * p.OH * p.OW);
-    const int oy = q / p.OW, ox = q - oy * p.OW;
-    const Lerp ly = lerp_coord(oy, p.H, p.OH, p.align_corners);
+    if (i >= (size_t)p.N * groups * p.OW) return;
+    const int t = (int)(i / p.OW), ox = (int)(i - (size_t)t * p.OW);
+    const int n = t / groups, oy0 = (t - n * groups) * U;
     const Lerp lx = lerp_coord(ox, p.W, p.OW, p.align_corners);
-    float best = -FLT_MAX;
-    int arg = 0;
+    Lerp ly[U];
+    float best[U];
+    int arg[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        ly[u] = lerp_coord(min(oy0 + u, p.OH - 1), p.H, p.OH, p.align_corners);
+        best[u] = -FLT_MAX;
+        arg[u] = 0;
+    }
     for (int s = 0; s < p.S; ++s) {
         const h8 *plane = p.x + ((size_t)s * p.N + n) * p.H * p.W;
-        const h8 v00 = plane[(size_t)ly.i0 * p.W + lx.i0], v01 = plane[(size_t)ly.i0 * p.W + lx.i1];
-        const h8 v10 = plane[(size_t)ly.i1 * p.W + lx.i0], v11 = plane[(size_t)ly.i1 * p.W + lx.i1];
+        float top[8], bot[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int ch = s * 8 + c;
-            if (ch >= p.C) break;
-            const float top = (1.0f - lx.f) * E::get(v00, c) + lx.f * E::get(v01, c);
-            const float bot = (1.0f - lx.f) * E::get(v10, c) + lx.f * E::get(v11, c);
-            const float v = (1.0f - ly.f) * top + ly.f * bot;
-            if (ch == 0 || v > best) {
-                best = v;
-                arg = ch;
+        for (int u = 0; u < U; ++u) {
+            if (u == 0 || ly[u].i0 != ly[u - 1].i0) {
+                const h8 *r0 = plane + (size_t)ly[u].i0 * p.W, *r1 = plane + (size_t)ly[u].i1 * p.W;
+                const h8 v00 = r0[lx.i0], v01 = r0[lx.i1], v10 = r1[lx.i0], v11 = r1[lx.i1];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    top[c] = (1.0f - lx.f) * E::get(v00, c) + lx.f * E::get(v01, c);
+                    bot[c] = (1.0f - lx.f) * E::get(v10, c) + lx.f * E::get(v11, c);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int ch = s * 8 + c;
+                if (ch >= p.C) break;
+                const float v = (1.0f - ly[u].f) * top[c] + ly[u].f * bot[c];
+                if (ch == 0 || v > best[u]) {
+                    best[u] = v;
+                    arg[u] = ch;
+                }
             }
         }
     }
-    ((int *)p.y)[i] = arg;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (oy0 + u < p.OH) ((int *)p.y)[((size_t)n * p.OH + oy0 + u) * p.OW + ox] = arg[u];
+}
+
+template <typename E, int U>
+static hipError_t launch_resize_argmax(const ResizeParams &p, hipStream_t st) {
+    const int groups = (p.OH + U - 1) / U;
+    launch((resize_argmax_kernel<E, U>), dim3(blocks_for((size_t)p.N * groups * p.OW, 256)), dim3(256), 0, st, p, groups);
+    return hipGetLastError();
 }
 
 hipError_t launch_resize(const ResizeParams &p, bool argmax, hipStream_t st) {
     const size_t opix = (size_t)p.N * p.OH * p.OW;
     if (!opix) return hipSuccess;
     if (argmax) {
-        if (p.bf16) launch(resize_argmax_kernel<BF16>, dim3(blocks_for(opix, 256)), dim3(256), 0, st, p);
-        else launch(resize_argmax_kernel<F16>, dim3(blocks_for(opix, 256)), dim3(256), 0, st, p);
+        // as many rows per thread as leave two workgroups per compute unit
+        const size_t per = opix / (512 * 256);
+        if (per >= 4) return p.bf16 ? launch_resize_argmax<BF16, 4>(p, st) : launch_resize_argmax<F16, 4>(p, st);
+        if (per >= 2) return p.bf16 ? launch_resize_argmax<BF16, 2>(p, st) : launch_resize_argmax<F16, 2>(p, st);
+        return p.bf16 ? launch_resize_argmax<BF16, 1>(p, st) : launch_resize_argmax<F16, 1>(p, st);
     } else {
         if (p.bf16) launch(resize_kernel<BF16>, dim3(blocks_for(opix * p.S, 256)), dim3(256), 0, st, p);
         else launch(resize_kernel<F16>, dim3(blocks_for(opix * p.S, 256)), dim3(256), 0, st, p);
