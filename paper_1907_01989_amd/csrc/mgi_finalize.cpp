@@ -201,6 +201,21 @@ void add_gemm_configs(Node &nd, size_t M) {
     }
 }
 
+// Output rows per thread of the 3x3 depthwise kernel: four at stride 1, two at
+// stride 2 (a row read once serves more outputs), halved while that leaves
+// less than one workgroup per compute unit: a lone wave per SIMD takes its
+// whole strip's 72 FMAs per row one after the other.  (v1's and v2's depthwise
+// layers on one image, whole networks in a graph: 117 us with four and two
+// rows, 111 with one; 193 and 185.)
+int pick_dw_rows(const Shape &out, int stride) {
+    int r = stride == 1 ? 4 : 2;
+    auto wgs = [&](int rows) {
+        return ((size_t)out.w * ((out.h + rows - 1) / rows) * slices(out.c) * out.n + 255) / 256;
+    };
+    while (r > 1 && wgs(r) < 256) r /= 2;
+    return r;
+}
+
 void add_pwdw_configs(Node &nd) {
     // channels per workgroup of the fused pointwise + depthwise kernel, and
     // the two separate kernels through the scratch tensor (pipelined GEMM
@@ -221,7 +236,7 @@ void add_pwdw_configs(Node &nd) {
     std::rotate(nd.cfgs.begin(), nd.cfgs.begin() + nd.pwdw_first, nd.cfgs.begin() + nd.pwdw_first + 1);
     GemmTile t;
     pick_pipe_tile(t, nd.dw_in.pixels(), nd.nb16 * 16);
-    const int dwr = nd.dw_conv.stride_h == 1 ? 4 : 2;
+    const int dwr = pick_dw_rows(nd.dw_out, nd.dw_conv.stride_h);
     const Node::Config split{t, dwr, "split_" + tile_name(t), true, 0};
     nd.cfgs.insert(nd.fused_default ? nd.cfgs.end() : nd.cfgs.begin(), Node::Config(split));
     if (nd.ksp % 8 == 0) {                // the GEMM with two K-steps per ring stage
@@ -277,7 +292,7 @@ void add_irb_configs(Node &nd) {
     }
     GemmTile t;
     pick_pipe_tile(t, s.pixels(), nd.nb16 * 16);
-    three.push_back(Node::Config{t, st == 1 ? 4 : 2, "split3_" + tile_name(t), true, 0, 2});
+    three.push_back(Node::Config{t, pick_dw_rows(d, st), "split3_" + tile_name(t), true, 0, 2});
     std::vector<Node::Config> order;
     auto add = [&](const std::vector<Node::Config> &v) { order.insert(order.end(), v.begin(), v.end()); };
     if (nd.irb_default) {
@@ -303,7 +318,7 @@ void add_stemdw_configs(const mgi_plan &p, Node &nd) {
         kern::stemdw_configs(q, c, nullptr, &name);
         nd.cfgs.push_back(Node::Config{GemmTile{}, 0, name, false, c});
     }
-    const Node::Config split{GemmTile{}, 4, "split", true, 0};
+    const Node::Config split{GemmTile{}, pick_dw_rows(nd.dw_out, 1), "split", true, 0};
     nd.cfgs.insert(nd.fused_default ? nd.cfgs.end() : nd.cfgs.begin(), Node::Config(split));
     nd.apply(0);
 }
@@ -414,13 +429,17 @@ void add_dwpw_configs(Node &nd) {
     }
 }
 
-// rows per thread of the 3x3 depthwise kernel (stride 1 or 2, dilation 1 or 2)
-void add_depthwise_configs(Node &nd) {
+// rows per thread of the 3x3 depthwise kernel (stride 1 or 2, dilation 1 or 2):
+// the default first, one row on small grids and eight (four) on large ones
+// among the alternatives
+void add_depthwise_configs(const mgi_plan &p, Node &nd) {
     if (nd.conv.kh != 3 || nd.conv.kw != 3 || nd.conv.stride_h != nd.conv.stride_w ||
         nd.conv.dil_h != nd.conv.dil_w || nd.conv.stride_h > 2 || nd.conv.dil_h > 2)
         return;
-    const int rows[2][3] = {{4, 2, 8}, {2, 1, 4}};
-    for (int r : rows[nd.conv.stride_h - 1]) nd.cfgs.push_back({GemmTile{}, r, "rows" + std::to_string(r)});
+    const int first = pick_dw_rows(p.bufs[nd.out].shape, nd.conv.stride_h);
+    std::vector<int> rows = nd.conv.stride_h == 1 ? std::vector<int>{4, 2, first < 4 ? 1 : 8} : std::vector<int>{2, 1, 4};
+    std::stable_partition(rows.begin(), rows.end(), [&](int r) { return r == first; });
+    for (int r : rows) nd.cfgs.push_back({GemmTile{}, r, "rows" + std::to_string(r)});
     nd.dw_rows = nd.cfgs[0].dw_rows;
 }
 
@@ -436,7 +455,7 @@ void add_configs(const mgi_plan &p, Node &nd, size_t M) {
         case NodeKind::FcSoftmax: add_fc_configs(nd, M); break;
         case NodeKind::GemmPool: add_pool_configs(nd); break;
         case NodeKind::DwPw: add_dwpw_configs(nd); break;
-        case NodeKind::Depthwise: add_depthwise_configs(nd); break;
+        case NodeKind::Depthwise: add_depthwise_configs(p, nd); break;
         default: break;
     }
 }

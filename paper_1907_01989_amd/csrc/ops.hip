@@ -391,9 +391,9 @@ hipError_t launch_depthwise(const DwParams &p, int rows, hipStream_t st) {
 #define MGI_DW_CASE(S_, D_, R_) \
         if (p.sh == S_ && p.dh == D_ && R == R_) \
             return p.bf16 ? launch_dw3<BF16, S_, D_, R_>(p, st) : launch_dw3<F16, S_, D_, R_>(p, st);
-        MGI_DW_CASE(1, 1, 2) MGI_DW_CASE(1, 1, 4) MGI_DW_CASE(1, 1, 8)
+        MGI_DW_CASE(1, 1, 1) MGI_DW_CASE(1, 1, 2) MGI_DW_CASE(1, 1, 4) MGI_DW_CASE(1, 1, 8)
         MGI_DW_CASE(2, 1, 1) MGI_DW_CASE(2, 1, 2) MGI_DW_CASE(2, 1, 4)
-        MGI_DW_CASE(1, 2, 2) MGI_DW_CASE(1, 2, 4) MGI_DW_CASE(1, 2, 8)
+        MGI_DW_CASE(1, 2, 1) MGI_DW_CASE(1, 2, 2) MGI_DW_CASE(1, 2, 4) MGI_DW_CASE(1, 2, 8)
         MGI_DW_CASE(2, 2, 1) MGI_DW_CASE(2, 2, 2) MGI_DW_CASE(2, 2, 4)
 #undef MGI_DW_CASE
         if (rows > 0) return hipErrorInvalidValue;

@@ -427,3 +427,32 @@ def test_concat_operands_written_in_place(chans, dtype):
         _, outs, _ = run_gpu(desc, materialize_all=False, dtype=dtype, planner=planner)
         for o, k in zip(outs, kept):
             np.testing.assert_array_equal(o, k)
+
+
+@pytest.mark.parametrize("n,h,w,c,s,d", [(1, 7, 5, 24, 1, 1), (1, 14, 14, 96, 1, 2), (2, 9, 8, 40, 2, 1),
+                                         (3, 33, 31, 64, 1, 1), (8, 56, 56, 128, 1, 1)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_depthwise_every_row_count(n, h, w, c, s, d, dtype):
+    # one row per thread on small grids, four (two) and eight (four) on large
+    # ones: the same bits from the sliced tensor
+    from paper_1907_01989_amd import engine, _binding as B
+    g = NetBuilder(seed=c + h)
+    y = g.dw(sliced(g, g.input(n, h, w, c, -1, 1)), 3, s, d, act=ACT_RELU6)
+    g.mark_output(y)
+    desc = g.graph(f"dwrows_{n}x{h}x{w}x{c}_s{s}d{d}")
+    if dtype:
+        desc = workloads.as_bf16_graph(desc)
+    ref = oracle.run_graph(desc)[y]
+    plan = engine.Plan(desc, bind=False, dtype=dtype)
+    i = [m["kind"] for m in plan.nodes()].index("dw_conv")
+    outs, names = [], []
+    for cfg in range(plan.node_configs()[i][1]):
+        B.mgi_plan_set_node_config(plan.handle, i, cfg)
+        names.append(plan.node_configs()[i][2])
+        _, o, _ = run_gpu(desc, materialize_all=False, dtype=dtype, configs={i: cfg})
+        outs.append(o[0])
+    log(f"[case] {desc['name']} dtype {dtype} {names}")
+    assert ("rows1" in names) == (s == 2 or n * h < 200) and len(set(names)) == 3
+    check_isolated("dw", outs[0], ref.reshape(outs[0].shape), rtol=ISO_RTOL_BF16 if dtype else ISO_RTOL)
+    for o in outs[1:]:
+        np.testing.assert_array_equal(o, outs[0])
