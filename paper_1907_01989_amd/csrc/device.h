@@ -238,17 +238,21 @@ __device__ __forceinline__ void wait_vm_lds() {
 
 // ---------------------------------------------------------------------------
 // Input band of a convolution over an NHWC graph input: rows [iy0, iy0 +
-// nrows) of image n, row r of the band at band + r * rs (16-bit storage
+// nrows) of image n of N, row r of the band at band + r * rs (16-bit storage
 // values, the data from column lead on).  The padding cells (rows outside
-// the image, columns before and after the data) are zeroed, then the rows
-// are copied with each thread loading NV units (16-byte vectors, or single
-// elements when rows are not 16-byte aligned) before storing any, so that a
-// workgroup's loads are in flight together.  A thread's place in a row is
-// found with one division; rows shorter than the workgroup are copied
-// several per pass.  The caller synchronises before reading the band.
+// the image, columns before and after the data) are zeroed, then the rows are
+// copied with each thread loading NV units of 16 bytes before storing any, so
+// that a workgroup's loads are in flight together.  Rows that are whole units:
+// a thread's place in a row is found with one division; rows shorter than the
+// workgroup are copied several per pass.  Other rows (an odd width): the
+// band's rows are one stretch of memory, read in aligned units whose values
+// are stored one by one (loading single values took eight times the loads,
+// and a memory latency per four of a thread's values: stem and depthwise of 50
+// images of 225 x 225 in 4-row bands 52.8 -> 33.2 us, of 16 fp32 images of
+// 193 x 193 20.3 -> 12.2).  The caller synchronises before reading the band.
 // ---------------------------------------------------------------------------
 template <typename E, typename TIN, int NT, int NV>
-__device__ __forceinline__ void stage_input_band(_Float16 *band, const TIN *x, int n, int H, int W, int C,
+__device__ __forceinline__ void stage_input_band(_Float16 *band, const TIN *x, int n, int N, int H, int W, int C,
                                                  int iy0, int nrows, int rs, int lead, int tid) {
     constexpr int VEC = 16 / sizeof(TIN);
     typedef TIN tv __attribute__((ext_vector_type(VEC)));
@@ -256,7 +260,6 @@ __device__ __forceinline__ void stage_input_band(_Float16 *band, const TIN *x, i
     const int r_lo = max(0, -iy0), r_hi = min(nrows, H - iy0);   // band rows inside the image
     const TIN *src0 = x + ((size_t)n * H + iy0) * rowlen;
     const bool vec = (rowlen % 8) == 0 && (lead % 8) == 0 && (rs % 8) == 0;
-    const int upr = vec ? rowlen / VEC : rowlen;                  // load units per row
     uint16_t *b16 = (uint16_t *)band;
     const int tail = rs - lead - rowlen;                         // zero columns after the data
     for (int r = 0; r < nrows; ++r) {
@@ -266,21 +269,54 @@ __device__ __forceinline__ void stage_input_band(_Float16 *band, const TIN *x, i
             for (int c = tid; c < rs; c += NT) b16[r * rs + c] = 0;
         }
     }
-    auto copy_unit = [&](int r, int c, const tv &v, TIN e) {
-        if (vec) {
-            _Float16 *dst = band + r * rs + lead + c * VEC;
-            float f[VEC];
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) f[i] = (float)v[i];
-            if (VEC == 8 && !E::bf) *(tv *)dst = v;                  // fp16 input, fp16 storage
-            else if (VEC == 8) *(h8 *)dst = E::pack(f);
-            else *(h4 *)dst = E::pack4(f);
-        } else {
-            b16[r * rs + lead + c] = E::bits((float)e);
-        }
-    };
     tv bv[NV];
-    TIN bs[NV];
+    if (!vec) {
+        const int count = (r_hi - r_lo) * rowlen;
+        if (count <= 0) return;
+        const TIN *first = src0 + (size_t)r_lo * rowlen;
+        const int skew = (int)(((uintptr_t)first & 15) / sizeof(TIN));   // values of the first unit before the band
+        const TIN *aligned = first - skew;
+        const int units = (skew + count + VEC - 1) / VEC;
+        // (units reach past the band, at the ends of the array past the
+        // array: there, single values)
+        const bool inside = aligned >= x && aligned + (size_t)units * VEC <= x + (size_t)N * H * rowlen;
+        for (int v0 = tid; v0 < units; v0 += NT * NV) {
+            if (inside) {
+#pragma unroll
+                for (int u = 0; u < NV; ++u) bv[u] = *(const tv *)(aligned + (size_t)min(v0 + u * NT, units - 1) * VEC);
+            } else {
+#pragma unroll
+                for (int u = 0; u < NV; ++u)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i)
+                        bv[u][i] = first[min(max((v0 + u * NT) * VEC + i - skew, 0), count - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < NV; ++u) {
+                const int e0 = (v0 + u * NT) * VEC - skew;           // the unit's first value in the band's data
+                int r = (int)((unsigned)(e0 + rowlen) / (unsigned)rowlen) - 1, c = e0 - r * rowlen;
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    if (e0 + i >= 0 && e0 + i < count) b16[(r_lo + r) * rs + lead + c] = E::bits((float)bv[u][i]);
+                    if (++c == rowlen) {
+                        c = 0;
+                        ++r;
+                    }
+                }
+            }
+        }
+        return;
+    }
+    const int upr = rowlen / VEC;                                 // units per row
+    auto copy_unit = [&](int r, int c, const tv &v) {
+        _Float16 *dst = band + r * rs + lead + c * VEC;
+        float f[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) f[i] = (float)v[i];
+        if (VEC == 8 && !E::bf) *(tv *)dst = v;                      // fp16 input, fp16 storage
+        else if (VEC == 8) *(h8 *)dst = E::pack(f);
+        else *(h4 *)dst = E::pack4(f);
+    };
     if (upr <= NT) {
         const int P = NT / upr;                                   // rows per pass
         const int rq = tid / upr, cq = tid - rq * upr;
@@ -289,15 +325,12 @@ __device__ __forceinline__ void stage_input_band(_Float16 *band, const TIN *x, i
 #pragma unroll
             for (int u = 0; u < NV; ++u) {
                 const int r = r_lo + (p0 + u) * P + rq;
-                if (rq < P && r < r_hi) {
-                    if (vec) bv[u] = *(const tv *)(src0 + (size_t)r * rowlen + cq * VEC);
-                    else bs[u] = src0[(size_t)r * rowlen + cq];
-                }
+                if (rq < P && r < r_hi) bv[u] = *(const tv *)(src0 + (size_t)r * rowlen + cq * VEC);
             }
 #pragma unroll
             for (int u = 0; u < NV; ++u) {
                 const int r = r_lo + (p0 + u) * P + rq;
-                if (rq < P && r < r_hi) copy_unit(r, cq, bv[u], bs[u]);
+                if (rq < P && r < r_hi) copy_unit(r, cq, bv[u]);
             }
         }
     } else {
@@ -306,15 +339,12 @@ __device__ __forceinline__ void stage_input_band(_Float16 *band, const TIN *x, i
 #pragma unroll
                 for (int u = 0; u < NV; ++u) {
                     const int c = c0 + u * NT + tid;
-                    if (c < upr) {
-                        if (vec) bv[u] = *(const tv *)(src0 + (size_t)r * rowlen + c * VEC);
-                        else bs[u] = src0[(size_t)r * rowlen + c];
-                    }
+                    if (c < upr) bv[u] = *(const tv *)(src0 + (size_t)r * rowlen + c * VEC);
                 }
 #pragma unroll
                 for (int u = 0; u < NV; ++u) {
                     const int c = c0 + u * NT + tid;
-                    if (c < upr) copy_unit(r, c, bv[u], bs[u]);
+                    if (c < upr) copy_unit(r, c, bv[u]);
                 }
             }
         }

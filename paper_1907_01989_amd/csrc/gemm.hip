@@ -984,7 +984,7 @@ __global__ __launch_bounds__(256) void stem_kernel(StemParams p, int th, int rs,
         a[i] = p.w[(size_t)i * 64 + lane];
         c0[i] = bias_frag(p.bias, i, p.nb16, lane);
     }
-    stage_input_band<E, TIN, 256, 4>(band, (const TIN *)p.x, n, p.H, p.W, p.C, iy0, nrows, rs, p.pl * p.C, tid);
+    stage_input_band<E, TIN, 256, 4>(band, (const TIN *)p.x, n, p.N, p.H, p.W, p.C, iy0, nrows, rs, p.pl * p.C, tid);
     // offsets of the lane's 8 im2col entries inside a window
     int koff[8];
 #pragma unroll

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(NT) void stemdw_kernel(StemDwParams p) {
         a[i] = p.w[(size_t)i * 64 + lane];
         c0[i] = bias_frag(p.bias, i, p.nb16, lane);
     }
-    stage_input_band<E, TIN, NT, 4>(band, (const TIN *)p.x, n, p.H, p.W, p.C, iy0, nrows, rs, p.pl * p.C, tid);
+    stage_input_band<E, TIN, NT, 4>(band, (const TIN *)p.x, n, p.N, p.H, p.W, p.C, iy0, nrows, rs, p.pl * p.C, tid);
     if (tid < NSL * 9) taps[tid] = tq;
     if (tid < NSL * 8) dwb[tid] = bq;
     if (tid == 0) *zslot = zero_h8();

@@ -106,3 +106,36 @@ def test_fused_stem_network(net):
     _, plain, _ = run_gpu(desc, materialize_all=False, fuse_stemdw=False)
     for a, b in zip(fused, plain):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("n,h,w,c,k", [(1, 17, 15, 3, 3), (3, 33, 31, 3, 3), (2, 66, 101, 3, 3), (1, 225, 225, 3, 3),
+                                       (2, 9, 7, 1, 5), (1, 40, 37, 4, 2), (2, 19, 350, 3, 3)])
+@pytest.mark.parametrize("dtype", [DTYPE_FP16, DTYPE_FP32])
+def test_rows_off_16_bytes(n, h, w, c, k, dtype):
+    """Images whose rows are not whole 16-byte units, starting anywhere, between
+    values that must not be read into the result; alone and with the
+    depthwise layer, in every configuration."""
+    import torch
+    from paper_1907_01989_amd import engine, _binding as B
+    g = NetBuilder(seed=h + w)
+    s = g.conv(g.input(n, h, w, c, 0, 1, dtype=dtype), 32, k, 2, act=ACT_RELU6)
+    g.mark_output(g.dw(s, 3))
+    desc = g.graph("rows")
+    ref = oracle.run_graph(desc)[2]
+    for fuse in (0, 2):
+        plan = engine.Plan(desc, fuse_stemdw=fuse)
+        x = plan.input_tensors()[0]
+        first = None
+        for cfg in range(plan.node_configs()[0][1]):
+            B.mgi_plan_set_node_config(plan.handle, 0, cfg)
+            log(f"[case] rows {n}x{h}x{w}x{c} k{k} input {dtype} {plan.node_configs()[0][2]}")
+            for off in (0, 1, 3, 6):
+                buf = torch.full((x.numel() + 32,), float("nan"), dtype=x.dtype, device=x.device)
+                xo = buf[8 + off:8 + off + x.numel()].view(x.shape)
+                xo.copy_(x)
+                out = plan.run([xo])[0].cpu().numpy()
+                if first is None:
+                    first = out
+                    ok, msg = check_layer("stem rows", first, ref.reshape(first.shape))
+                    assert ok, msg
+                np.testing.assert_array_equal(out, first, err_msg=f"offset {off}")
