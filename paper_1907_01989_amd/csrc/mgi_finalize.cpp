@@ -306,6 +306,22 @@ void add_irb_configs(Node &nd) {
     nd.apply(0);
 }
 
+// The fused stem + depthwise configuration listed first, and whether it gets
+// at least 128 workgroups: the first band height (4 rows), or the next (2 rows)
+// where that takes more than half a compute unit's LDS (14 images of 321 x 321
+// 32.2 us against 27.0) or only the shorter bands make 128 workgroups (5
+// images of 115 x 115 9.8 us as two kernels against 5.9).  -1: none fits.
+int pick_stemdw(const kern::StemDwParams &q, bool *fills) {
+    kern::StemDwGeom g[2]{};
+    const int n = std::min(2, kern::stemdw_configs(q, -1, nullptr, nullptr));
+    for (int c = 0; c < n; ++c) (void)kern::stemdw_configs(q, c, &g[c], nullptr);
+    auto enough = [&](int c) { return (size_t)q.N * g[c].nbands >= 128; };
+    int first = n > 0 ? 0 : -1;
+    if (n > 1 && !g[1].roll && enough(1) && (!enough(0) || g[0].lds > 80 * 1024)) first = 1;
+    *fills = first >= 0 && enough(first);
+    return first;
+}
+
 void add_stemdw_configs(const mgi_plan &p, Node &nd) {
     // band heights of the fused stem + depthwise kernel, and the two
     // separate kernels through the scratch tensor (first when the fused
@@ -318,6 +334,7 @@ void add_stemdw_configs(const mgi_plan &p, Node &nd) {
         kern::stemdw_configs(q, c, nullptr, &name);
         nd.cfgs.push_back(Node::Config{GemmTile{}, 0, name, false, c});
     }
+    std::rotate(nd.cfgs.begin(), nd.cfgs.begin() + nd.pwdw_first, nd.cfgs.begin() + nd.pwdw_first + 1);
     const Node::Config split{GemmTile{}, pick_dw_rows(nd.dw_out, 1), "split", true, 0};
     nd.cfgs.insert(nd.fused_default ? nd.cfgs.end() : nd.cfgs.begin(), Node::Config(split));
     nd.apply(0);
@@ -654,9 +671,10 @@ void fuse_stem_into_dw(mgi_plan &p, bool always) {
         t.dw_out = p.bufs[dw.out].shape;
         kern::StemDwParams q{};
         stemdw_shape(p, t, q);
-        kern::StemDwGeom geo{};
-        if (kern::stemdw_configs(q, 0, &geo, nullptr) == 0) continue;
-        t.fused_default = always || (size_t)q.N * geo.nbands >= 128;
+        bool fills = false;
+        t.pwdw_first = pick_stemdw(q, &fills);
+        if (t.pwdw_first < 0) continue;
+        t.fused_default = always || fills;
         t.kname = "stem_dw";
         t.dw_op = dw.op;
         t.out = dw.out;

@@ -165,7 +165,7 @@ struct Node {
     int scratch = -1;
     bool split = false;
     bool fused_default = true;
-    int pwdw_first = 0;         // PwDw: the fused kernel's configuration that is listed first
+    int pwdw_first = 0;         // PwDw / StemDw: the fused kernel's configuration that is listed first
     bool irb_default = false;   // Irb: the block kernel is the default configuration
     int pwdw_cfg = 0;       // PwDw / StemDw: configuration of the fused kernel (pwdw_configs,
                             // stemdw_configs)
