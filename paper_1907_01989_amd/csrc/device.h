@@ -43,6 +43,13 @@ __device__ __forceinline__ void divmod_fast(int x, int d, double inv, int &q, in
     }
 }
 
+// the same for 0 <= x < 2^16, 1 <= d < 2^16, from inv = ceil(2^32 / d) (0 for
+// d = 1, whose quotient is x itself)
+__device__ __forceinline__ void divmod_u16(int x, int d, unsigned inv, int &q, int &r) {
+    q = d == 1 ? x : (int)__umulhi((unsigned)x, inv);
+    r = x - q * d;
+}
+
 // Workgroups are dispatched to the 8 XCDs round-robin (block b -> XCD b % 8).
 // Give every XCD a contiguous range of tiles so that tiles sharing input rows
 // (same pixel block, neighbouring channel blocks) meet in the same L2.

@@ -221,7 +221,7 @@ bool depthwise_reads_nhwc(int KH, int KW, int sh, int sw, int dh, int dw, int N,
 struct DwTile {
     int rb, nrb, wp, nbands;
     size_t lds;
-    double inv_wp, inv_ow, inv_nsl[2], inv_nrb[2];
+    unsigned inv_wp, inv_ow, inv_nsl[2], inv_nrb[2], inv_strip[2];   // (see divmod_u16)
 };
 
 // Pointwise convolution fused with the depthwise 3x3 convolution (dilation 1,

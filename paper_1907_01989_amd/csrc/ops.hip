@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256) void dw3_kernel(DwParams p, int nstrips, DivCo
 // taps fit in registers also when bf16 ones are widened to fp32) of one output
 // column and R rows.  Bound by vector issue (25 * 8 FMAs per output element,
 // 2.1 us of the chip's at this size) and the staging round trip before it:
-// 10.8 us from the NHWC input of either type, and nothing for the conversion
+// 10.2 us from the NHWC input of either type, and nothing for the conversion
 // (7.5 us fp16, 10.2 fp32); 11.0 with bf16 storage (16.2); one image 4.9
 // (7.7).  SRC as above.
 // ---------------------------------------------------------------------------
@@ -203,8 +203,10 @@ __global__ __launch_bounds__(256) void dw5_kernel(DwParams p, DwTile q) {
     const int nrb = (rows - 1) * S_ + K, wp = q.wp;         // band: [TS][nrb][wp], first column -pl
     const int iy0 = oy0 * S_ - p.pt;
     h8 *taps = lds + TS * q.nrb * wp;                        // [TS][25]
-    // taps and the band; cells outside the input are zero
+    float *bias8 = (float *)(taps + TS * K * K);             // [TS][8]
+    // taps, biases and the band; cells outside the input are zero
     for (int e = tid; e < nsl * K * K; e += 256) taps[e] = p.w[(size_t)s0 * (K * K) + e];
+    if (tid < nsl * 8) bias8[tid] = p.bias[s0 * 8 + tid];
     const El *xin = SRC ? (const El *)p.xin + (size_t)n * p.H * p.W * p.S + s0
                         : (const El *)p.x + ((size_t)s0 * p.N + n) * p.H * p.W;
     const size_t xs = SRC ? 1 : (size_t)p.N * p.H * p.W;     // elements between slices
@@ -219,11 +221,11 @@ __global__ __launch_bounds__(256) void dw5_kernel(DwParams p, DwTile q) {
             const int e = e0 + u * 256;
             int sl, r, c, t;
             if (SRC) {                                       // slice fastest
-                divmod_fast(min(e, cells - 1), nsl, q.inv_nsl[nsl == TS ? 0 : 1], t, sl);
-                divmod_fast(t, wp, q.inv_wp, r, c);
+                divmod_u16(min(e, cells - 1), nsl, q.inv_nsl[nsl == TS ? 0 : 1], t, sl);
+                divmod_u16(t, wp, q.inv_wp, r, c);
             } else {                                         // column fastest
-                divmod_fast(min(e, cells - 1), wp, q.inv_wp, t, c);
-                divmod_fast(t, nrb, rows == q.rb ? q.inv_nrb[0] : q.inv_nrb[1], sl, r);
+                divmod_u16(min(e, cells - 1), wp, q.inv_wp, t, c);
+                divmod_u16(t, nrb, rows == q.rb ? q.inv_nrb[0] : q.inv_nrb[1], sl, r);
             }
             const int iy = iy0 + r, ix = c - p.pl;
             const bool in = iy >= 0 && iy < p.H && ix >= 0 && ix < p.W;
@@ -241,16 +243,15 @@ __global__ __launch_bounds__(256) void dw5_kernel(DwParams p, DwTile q) {
     const int nstrip = (rows + R - 1) / R, ntask = nsl * nstrip * p.OW * 2;
     for (int t0 = tid; t0 < ntask; t0 += 256) {
         const int half = t0 & 1;
-        int t, ox;
-        divmod_fast(t0 >> 1, p.OW, q.inv_ow, t, ox);
-        const int sl = t / nstrip, strip = t - sl * nstrip;
+        int t, ox, sl, strip;
+        divmod_u16(t0 >> 1, p.OW, q.inv_ow, t, ox);
+        divmod_u16(t, nstrip, rows == q.rb ? q.inv_strip[0] : q.inv_strip[1], sl, strip);
         const h4 *w4 = (const h4 *)(taps + sl * (K * K)) + half;
         h4 w[K * K];
 #pragma unroll
         for (int i = 0; i < K * K; ++i) w[i] = w4[2 * i];
-        float bias[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) bias[c] = p.bias[(s0 + sl) * 8 + half * 4 + c];
+        const f4 b4 = *((const f4 *)(bias8 + sl * 8) + half);
+        const float bias[4] = {b4[0], b4[1], b4[2], b4[3]};
         float acc[R][4];
         const h4 *row = (const h4 *)(lds + (sl * nrb + strip * R * S_) * wp + ox * S_) + half;
 #pragma unroll
@@ -332,35 +333,62 @@ static hipError_t launch_dw3(DwParams p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Band of the 5x5 kernel: as many slices (up to eight) and then strips (up to
-// two) per workgroup as keep 64 KiB of LDS and two workgroups per compute unit
-// (fewer, where even one slice and strip give less); 0 slices: no band fits.
-static DwTile dw5_tile(int N, int S, int OH, int OW, int sh, int &ls) {
-    DwTile t{};
-    const int R = 4 / sh;
-    t.wp = (OW - 1) * sh + 5;
-    auto lds = [&](int l, int rb) { return (size_t)(1 << l) * (((size_t)(rb - 1) * sh + 5) * t.wp + 25) * 16; };
-    auto wgs = [&](int l, int rb) { return (((size_t)S + (1 << l) - 1) >> l) * N * ((OH + rb - 1) / rb); };
-    ls = nhwc_slices(S);
-    while (ls > 0 && (lds(ls, R) > 65536 || wgs(ls, R) < 512)) --ls;
-    t.rb = lds(ls, 2 * R) <= 65536 && wgs(ls, 2 * R) >= 512 ? 2 * R : R;
-    t.nrb = (t.rb - 1) * sh + 5;
-    t.nbands = (OH + t.rb - 1) / t.rb;
-    t.lds = lds(ls, t.rb);
-    if (t.lds > 65536 || wgs(ls, t.rb) > 0x7fffffffull) t.nbands = 0;
-    return t;
+// Band of the 5x5 kernel: slices (2^ls) and output rows per workgroup.  Short
+// bands of few slices repeat more of their rows and fill fewer threads, tall
+// ones of many leave a compute unit one workgroup, whose loads nothing hides.
+// The estimate counts, for the workgroups per compute unit, a workgroup's
+// staging passes (3 each, of 256 cells, 5 where they read single slices of an
+// NHWC input, 16 bytes a pixel; two workgroups' worth is not hidden) and
+// computing passes (20 each, of 256 tasks), and 30 for each round of as many
+// workgroups as run at a time (by LDS, and by registers five of fp16, two of
+// bf16, whose taps are held as floats).  Over 20 sizes of both strides and
+// types its choice is 2.4 % over the best of the twelve on average, at most
+// 15 %.  (With as many slices and rows as 64 KiB and 512 workgroups allow
+// 38 x 55 x 55 x 48 took 23.0 us, now 16.6; 16 x 28 x 28 x 240 11.1, now 10.2;
+// bf16 8 x 28 x 28 x 240 11.6, now 7.1; stride 2, 16 x 56 x 56 x 96, 7.2, now
+// 7.9.)
+static DwTile dw5_tile(int N, int S, int OH, int OW, int sh, bool nhwc, bool bf16, int &ls_out) {
+    const int R = 4 / sh, K = 5;
+    DwTile best{};
+    size_t best_cost = 0;
+    for (int ls = nhwc_slices(S); ls >= 0; --ls)
+        for (int rb : {R, 2 * R, 4 * R}) {
+            if (rb > R && rb >= OH + R) break;
+            DwTile t{};
+            t.rb = rb;
+            t.wp = (OW - 1) * sh + K;
+            t.nrb = (rb - 1) * sh + K;
+            t.nbands = (OH + rb - 1) / rb;
+            const size_t TS = (size_t)1 << ls;
+            t.lds = TS * ((size_t)t.nrb * t.wp + K * K) * 16 + TS * 32;
+            const size_t wgs = ((size_t)S + TS - 1) / TS * N * t.nbands, cells = TS * t.nrb * t.wp;
+            if (t.lds > 65536 || cells >= 65536 || wgs > 0x7fffffffull) continue;
+            const size_t nsl = std::min<size_t>(TS, S), per = (wgs + 255) / 256;
+            const size_t stage = (nsl * t.nrb * t.wp + 255) / 256, comp = (nsl * (rb / R) * OW * 2 + 255) / 256;
+            const size_t conc = std::min<size_t>(bf16 ? 2 : 5, 163840 / t.lds);
+            const size_t cost = (per * (nhwc && ls == 0 ? 5 : 3) + 6) * stage + per * comp * 20 + (per + conc - 1) / conc * 30;
+            if (best.nbands == 0 || cost < best_cost) {
+                best = t;
+                best_cost = cost;
+                ls_out = ls;
+            }
+        }
+    return best;
 }
 
 template <typename E, int S_>
 static hipError_t launch_dw5(DwParams p, DwTile t, hipStream_t st) {
-    const int last = p.OH - (t.nbands - 1) * t.rb;          // rows of the last band
-    const int tail = p.S - ((p.S - 1) >> p.ls << p.ls);     // slices of the last group
-    t.inv_wp = 1.0 / t.wp;
-    t.inv_ow = 1.0 / p.OW;
-    t.inv_nsl[0] = 1.0 / (1 << p.ls);
-    t.inv_nsl[1] = 1.0 / tail;
-    t.inv_nrb[0] = 1.0 / t.nrb;
-    t.inv_nrb[1] = 1.0 / ((last - 1) * p.sh + 5);
+    const int R = 4 / S_, last = p.OH - (t.nbands - 1) * t.rb;   // rows of the last band
+    const int tail = p.S - ((p.S - 1) >> p.ls << p.ls);          // slices of the last group
+    auto inv = [](int d) { return (unsigned)((0x100000000ull + d - 1) / d); };
+    t.inv_wp = inv(t.wp);
+    t.inv_ow = inv(p.OW);
+    t.inv_nsl[0] = inv(1 << p.ls);
+    t.inv_nsl[1] = inv(tail);
+    t.inv_nrb[0] = inv(t.nrb);
+    t.inv_nrb[1] = inv((last - 1) * p.sh + 5);
+    t.inv_strip[0] = inv((t.rb + R - 1) / R);
+    t.inv_strip[1] = inv((last + R - 1) / R);
     const dim3 grid((unsigned)(t.nbands * p.N * ((p.S + (1 << p.ls) - 1) >> p.ls))), block(256);
     if (!p.xin) launch((dw5_kernel<E, S_, 0>), grid, block, (unsigned)t.lds, st, p, t);
     else if (p.xin_fp16) launch((dw5_kernel<E, S_, 1>), grid, block, (unsigned)t.lds, st, p, t);
@@ -379,7 +407,7 @@ static bool dw5_window(int KH, int KW, int sh, int sw, int dh, int dw) {
 bool depthwise_reads_nhwc(int KH, int KW, int sh, int sw, int dh, int dw, int N, int S, int OH, int OW) {
     int ls;
     return dw3_window(KH, KW, sh, sw, dh, dw) ||
-           (dw5_window(KH, KW, sh, sw, dh, dw) && dw5_tile(N, S, OH, OW, sh, ls).nbands > 0);
+           (dw5_window(KH, KW, sh, sw, dh, dw) && dw5_tile(N, S, OH, OW, sh, true, false, ls).nbands > 0);
 }
 
 hipError_t launch_depthwise(const DwParams &p, int rows, hipStream_t st) {
@@ -400,7 +428,7 @@ hipError_t launch_depthwise(const DwParams &p, int rows, hipStream_t st) {
     }
     if (dw5_window(p.KH, p.KW, p.sh, p.sw, p.dh, p.dw)) {
         DwParams q = p;
-        const DwTile t = dw5_tile(p.N, p.S, p.OH, p.OW, p.sh, q.ls);
+        const DwTile t = dw5_tile(p.N, p.S, p.OH, p.OW, p.sh, p.xin != nullptr, p.bf16, q.ls);
         if (t.nbands > 0) {
             if (p.sh == 1) return p.bf16 ? launch_dw5<BF16, 1>(q, t, st) : launch_dw5<F16, 1>(q, t, st);
             return p.bf16 ? launch_dw5<BF16, 2>(q, t, st) : launch_dw5<F16, 2>(q, t, st);

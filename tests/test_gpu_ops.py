@@ -429,6 +429,30 @@ def test_concat_operands_written_in_place(chans, dtype):
             np.testing.assert_array_equal(o, k)
 
 
+@pytest.mark.parametrize("n,h,w,c,s", [
+    (64, 7, 7, 104, 1), (64, 7, 6, 168, 1),      # eight slices a workgroup (the last of five), two bands and one
+    (33, 14, 13, 104, 1), (20, 30, 28, 40, 1),   # two slices, a last group of one; bands of sixteen and eight rows
+    (6, 40, 40, 56, 1), (1, 9, 200, 24, 1),      # bands of four rows; single slices of wide rows
+    (7, 61, 33, 24, 1),                          # a last band of five rows of eight
+    (30, 29, 27, 56, 2), (40, 21, 19, 72, 2),    # stride 2
+])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_depthwise_5x5_bands(n, h, w, c, s, dtype):
+    # the bands chosen by size, from the sliced tensor and from the NHWC input
+    for direct in (False, True):
+        g = NetBuilder(seed=c + h)
+        x = g.input(n, h, w, c, -1, 1, dtype=2 if dtype else 0)
+        y = g.dw(x if direct else sliced(g, x), 5, s, act=ACT_RELU6)
+        g.mark_output(y)
+        desc = g.graph(f"dw5_{n}x{h}x{w}x{c}_s{s}_{int(direct)}")
+        if dtype:
+            desc = workloads.as_bf16_graph(desc)
+        log(f"[case] {desc['name']} store {dtype}")
+        ref = oracle.run_graph(desc)[y]
+        _, outs, _ = run_gpu(desc, materialize_all=False, dtype=dtype)
+        check_isolated("dw", outs[0], ref.reshape(outs[0].shape), rtol=ISO_RTOL_BF16 if dtype else ISO_RTOL)
+
+
 @pytest.mark.parametrize("n,h,w,c,s,d", [(1, 7, 5, 24, 1, 1), (1, 14, 14, 96, 1, 2), (2, 9, 8, 40, 2, 1),
                                          (3, 33, 31, 64, 1, 1), (8, 56, 56, 128, 1, 1)])
 @pytest.mark.parametrize("dtype", [0, 1])
