@@ -467,44 +467,79 @@ __device__ __forceinline__ void store_tile_c8(const GemmParams &p, const f4 (&ac
     }
 }
 
-// Softmax of one fp32 row of `cols` values by one wave: up to 1024 columns
-// are held in registers (16 per lane, all loads issued at once; columns past
-// the end repeat the last one, which leaves the max unchanged and is kept out
-// of the sum), longer rows take a looped path; max and sum reduce by a fixed
-// butterfly.  The standalone softmax kernel and the FC kernel's fused softmax
-// both use it, so the two forms round alike.  softmax_load / softmax_finish
-// are its two halves for rows of at most kSoftmaxRegCols columns (a caller
-// may load several rows before finishing any).
-constexpr int kSoftmaxPer = 16, kSoftmaxRegCols = 64 * kSoftmaxPer;
-__device__ inline void softmax_load(const float *zr, int cols, int lane, float (&v)[kSoftmaxPer]) {
+// Softmax of fp32 rows of `cols` values by one wave: up to 1024 columns are
+// held in registers (2, 6 or 16 per lane, all loads issued at once; columns
+// past the end repeat the last one, which leaves the max unchanged and is kept
+// out of the sum), longer rows take a looped path; max and sum reduce by a
+// fixed butterfly.  U rows, r0, r0 + rs, .., are finished together: a row
+// alone waits for twelve dependent cross-lane steps and its exponentials, and
+// four one after the other made the FC kernel's last workgroup take longer
+// than its GEMM (with it, before and now: 16 rows of 87 classes 9.6 us and
+// 5.7, 9 of 300 9.5 and 6.6; 16 of 1000, bound by the exponentials of one
+// workgroup, 10.6 and 9.3).
+// The standalone softmax kernel and the FC kernel's fused softmax both use it,
+// so the two forms round alike, for any PER that holds the row.
+constexpr int kSoftmaxRegCols = 64 * 16;
+template <int PER, int U>
+__device__ inline void softmax_regs(const float *z, float *y, int r0, int rs, int rows, int cols, int lane) {
+    float v[U][PER], m[U], s[U];
 #pragma unroll
-    for (int i = 0; i < kSoftmaxPer; ++i) v[i] = zr[min(lane + 64 * i, cols - 1)];
-}
-__device__ inline void softmax_finish(float (&v)[kSoftmaxPer], float *yr, int cols, int lane) {
-    constexpr int PER = kSoftmaxPer;
-    float m = -FLT_MAX;
+    for (int u = 0; u < U; ++u) {
+        const float *zr = z + (size_t)min(r0 + u * rs, rows - 1) * cols;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) m = fmaxf(m, v[i]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    float s = 0.0f;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        v[i] = expf(v[i] - m);
-        s += lane + 64 * i < cols ? v[i] : 0.0f;
+        for (int i = 0; i < PER; ++i) v[u][i] = zr[min(lane + 64 * i, cols - 1)];
     }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    const float inv = 1.0f / s;
+    for (int u = 0; u < U; ++u) {
+        m[u] = -FLT_MAX;
 #pragma unroll
-    for (int i = 0; i < PER; ++i)
-        if (lane + 64 * i < cols) yr[lane + 64 * i] = v[i] * inv;
+        for (int i = 0; i < PER; ++i) m[u] = fmaxf(m[u], v[u][i]);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        float o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) o[u] = __shfl_xor(m[u], off, 64);
+#pragma unroll
+        for (int u = 0; u < U; ++u) m[u] = fmaxf(m[u], o[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        s[u] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            v[u][i] = expf(v[u][i] - m[u]);
+            s[u] += lane + 64 * i < cols ? v[u][i] : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        float o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) o[u] = __shfl_xor(s[u], off, 64);
+#pragma unroll
+        for (int u = 0; u < U; ++u) s[u] += o[u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (r0 + u * rs >= rows) break;
+        float *yr = y + (size_t)(r0 + u * rs) * cols;
+        const float inv = 1.0f / s[u];
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (lane + 64 * i < cols) yr[lane + 64 * i] = v[u][i] * inv;
+    }
+}
+// the same for the fewest registers that hold the row
+template <int U>
+__device__ inline void softmax_rows(const float *z, float *y, int r0, int rs, int rows, int cols, int lane) {
+    if (cols <= 64 * 2) softmax_regs<2, U>(z, y, r0, rs, rows, cols, lane);
+    else if (cols <= 64 * 6) softmax_regs<6, U>(z, y, r0, rs, rows, cols, lane);
+    else softmax_regs<16, U>(z, y, r0, rs, rows, cols, lane);
 }
 __device__ inline void softmax_row(const float *zr, float *yr, int cols, int lane) {
     if (cols <= kSoftmaxRegCols) {
-        float v[kSoftmaxPer];
-        softmax_load(zr, cols, lane, v);
-        softmax_finish(v, yr, cols, lane);
+        softmax_rows<1>(zr, yr, 0, 1, 1, cols, lane);
         return;
     }
     float m = -FLT_MAX;

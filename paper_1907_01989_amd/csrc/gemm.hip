@@ -916,16 +916,10 @@ __global__ __launch_bounds__(256) void fc_kernel(GemmParams p) {
         float *prob = p.sm_y + (size_t)m0 * p.cout;
         const int rows = min(16 * FM, p.M - m0);
         if (p.cout <= kSoftmaxRegCols) {
-            // rows wave, wave + 4, ...: a wave loads up to four rows before
-            // finishing any (one memory round trip per four rows)
+            // rows wave, wave + 4, ..: up to four of a wave at a time
             for (int r0 = wave; r0 < rows; r0 += 16) {
-                float v[4][kSoftmaxPer];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (r0 + 4 * u < rows) softmax_load(z + (size_t)(r0 + 4 * u) * p.cout, p.cout, lane, v[u]);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (r0 + 4 * u < rows) softmax_finish(v[u], prob + (size_t)(r0 + 4 * u) * p.cout, p.cout, lane);
+                if (r0 + 4 < rows) softmax_rows<4>(z, prob, r0, 4, rows, p.cout, lane);
+                else softmax_rows<1>(z, prob, r0, 4, rows, p.cout, lane);
             }
         } else {
             for (int r = wave; r < rows; r += 4)

@@ -357,16 +357,21 @@ void add_fc_configs(Node &nd, size_t M) {
         nd.cfgs.push_back({t, 0, "fc" + std::to_string(16 * o[0]) + "k" + std::to_string(o[1])});
     }
     if (nd.kind == NodeKind::FcSoftmax) {
-        // FC into the logits, then the softmax kernel: first when there
-        // is more than one tile of 16 rows (each arriving workgroup's L2
-        // write-back costs more than the softmax launch it saves once
-        // the grid has a few hundred workgroups: 16.1 us fused against
-        // 10.6 us split for 64 rows of 1000 classes, 7.2 against 9.6 us
-        // for one row)
+        // FC into the logits, then the softmax kernel: first when there is
+        // more than one tile of 16 rows (each arriving workgroup's L2
+        // write-back costs more than the softmax launch it saves once the
+        // grid has a few hundred workgroups: 12.3 us fused against 9.2 us
+        // split for 64 rows of 1000 classes, 5.6 against 9.1 for one row),
+        // unless the rows have at most 384 classes (few exponentials per lane
+        // of the one workgroup that finishes a tile) and the grid at most 96
+        // workgroups: 48 rows of 10 classes 5.1 us fused / 9.0 split, 128 of
+        // 100 7.2 / 9.1, 64 of 384 8.0 / 9.2, 128 of 200 (104) 8.5 / 9.1,
+        // 128 of 384 (192) 9.7 / 9.0, 24 of 600 9.6 / 9.3
         Node::Config split = nd.cfgs[0];
         split.name = "split_" + split.name;
         split.split = true;
-        nd.cfgs.insert(M > 16 ? nd.cfgs.begin() : nd.cfgs.end(), split);
+        const bool fused = M <= 16 || (nd.nb16 * 16 <= 384 && (M + 15) / 16 * (size_t)nd.nb16 <= 96);
+        nd.cfgs.insert(fused ? nd.cfgs.end() : nd.cfgs.begin(), split);
     }
     nd.apply(0);
 }

@@ -75,6 +75,28 @@ def test_fused_fc_softmax(n, K, classes):
     np.testing.assert_allclose(outs[0].sum(axis=-1), 1.0, rtol=1e-5)
 
 
+@pytest.mark.parametrize("n,classes,first", [
+    (1, 1, "fc"), (16, 64, "fc"), (17, 128, "fc"), (33, 129, "fc"), (64, 384, "fc"), (65, 384, "split"),
+    (19, 385, "split"), (21, 1024, "split"), (15, 1025, "fc"), (256, 96, "fc"), (257, 96, "split")])
+def test_rows_in_registers(n, classes, first):
+    # every register count of the row routine at its edges, a tile's rows
+    # finished together (full, ragged and single), and which form comes first
+    from paper_1907_01989_amd import engine
+    desc, y = head_graph(n, 72, classes)
+    plan = engine.Plan(desc, bind=False)
+    idx = fused_index(plan)
+    names = plan.node_configs()[idx]
+    log(f"[case] {desc['name']} {names}")
+    assert names[2].startswith(first)
+    _, plain, _ = run_gpu(desc, materialize_all=False, fuse_softmax=False)
+    for cf in range(names[1]):
+        _, o, _ = run_gpu(desc, materialize_all=False, configs={idx: cf})
+        np.testing.assert_array_equal(o[0], plain[0], err_msg=f"configuration {cf}")
+    ref = oracle.run_graph(desc, keep=[y])[y]
+    ok, msg = check_layer("probabilities", plain[0], ref.reshape(plain[0].shape))
+    assert ok, msg
+
+
 def test_counters_return_to_zero():
     import torch
     from paper_1907_01989_amd import engine, _binding as B
