@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "kernels.h"
+#include "rowunit.h"
 
 namespace mgi {
 namespace kern {
@@ -301,7 +302,7 @@ __device__ __forceinline__ void stage_input_band(_Float16 *band, const TIN *x, i
 #pragma unroll
             for (int u = 0; u < NV; ++u) {
                 const int e0 = (v0 + u * NT) * VEC - skew;           // the unit's first value in the band's data
-                int r = (int)((unsigned)(e0 + rowlen) / (unsigned)rowlen) - 1, c = e0 - r * rowlen;
+                int r = unit_row(e0, rowlen, VEC), c = e0 - r * rowlen;
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) {
                     if (e0 + i >= 0 && e0 + i < count) b16[(r_lo + r) * rs + lead + c] = E::bits((float)bv[u][i]);

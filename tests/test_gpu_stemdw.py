@@ -139,3 +139,43 @@ def test_rows_off_16_bytes(n, h, w, c, k, dtype):
                     ok, msg = check_layer("stem rows", first, ref.reshape(first.shape))
                     assert ok, msg
                 np.testing.assert_array_equal(out, first, err_msg=f"offset {off}")
+
+
+@pytest.mark.parametrize("n,h,w,c", [(3, 5, 1, 1), (3, 5, 2, 1), (2, 5, 3, 1), (3, 7, 4, 1), (2, 9, 5, 1), (3, 5, 6, 1),
+                                     (3, 5, 1, 3), (2, 9, 2, 3), (3, 7, 1, 5), (4, 40, 1, 2)])
+@pytest.mark.parametrize("dtype", [DTYPE_FP16, DTYPE_FP32])
+def test_rows_shorter_than_a_unit(n, h, w, c, dtype):
+    """Images whose rows are shorter than the 16-byte units they are read in, so
+    that a band may start more than a row into its first unit: at every offset,
+    alone and with the depthwise layer, in every configuration."""
+    import torch
+    from paper_1907_01989_amd import engine, _binding as B
+    k = 3 if c <= 3 else 2
+    g = NetBuilder(seed=10 * h + w + c)
+    s = g.conv(g.input(n, h, w, c, 0, 1, dtype=dtype), 32, k, 1, act=ACT_RELU6)
+    g.mark_output(s)
+    alone = g.graph("short rows")
+    g = NetBuilder(seed=10 * h + w + c)
+    s = g.conv(g.input(n, h, w, c, 0, 1, dtype=dtype), 32, k, 1, act=ACT_RELU6)
+    g.mark_output(g.dw(s, 3))
+    pair = g.graph("short rows")
+    for desc, fuses in ((alone, (0,)), (pair, (0, 2))):
+        ref = oracle.run_graph(desc)[desc["outputs"][0]]
+        first = None
+        for fuse in fuses:
+            plan = engine.Plan(desc, fuse_stemdw=fuse)
+            assert plan.nodes()[0]["kind"] in ("conv_stem", "stem_dw")
+            x = plan.input_tensors()[0]
+            for cfg in range(plan.node_configs()[0][1]):
+                B.mgi_plan_set_node_config(plan.handle, 0, cfg)
+                log(f"[case] short rows {n}x{h}x{w}x{c} input {dtype} {plan.node_configs()[0][2]}")
+                for off in range(8):
+                    buf = torch.full((x.numel() + 32,), float("nan"), dtype=x.dtype, device=x.device)
+                    xo = buf[8 + off:8 + off + x.numel()].view(x.shape)
+                    xo.copy_(x)
+                    out = plan.run([xo])[0].cpu().numpy()
+                    if first is None:
+                        first = out
+                        ok, msg = check_layer("short rows", first, ref.reshape(first.shape))
+                        assert ok, msg
+                    np.testing.assert_array_equal(out, first, err_msg=f"offset {off}")
