@@ -307,9 +307,12 @@ def _ptr_array(n):
     return t
 
 
-def plan_run_ptrs(p, in_ptrs, out_ptrs, stream):
-    """mgi_plan_run for a caller that has checked the pointer counts against the plan."""
-    status = _lib.mgi_plan_run(p, _ptr_array(len(in_ptrs))(*in_ptrs), _ptr_array(len(out_ptrs))(*out_ptrs), stream)
+def plan_run_ptrs(p, n_in, n_out, in_ptrs, out_ptrs, stream):
+    """mgi_plan_run for a caller that knows the plan's input and output counts."""
+    if len(in_ptrs) != n_in or len(out_ptrs) != n_out:
+        raise ValueError(f"plan takes {n_in} inputs and {n_out} outputs, "
+                         f"got {len(in_ptrs)} and {len(out_ptrs)}")
+    status = _lib.mgi_plan_run(p, _ptr_array(n_in)(*in_ptrs), _ptr_array(n_out)(*out_ptrs), stream)
     if status != MGI_OK:
         _check(status)
 

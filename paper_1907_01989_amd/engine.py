@@ -204,8 +204,8 @@ class Plan:
         if not (isinstance(inputs, (list, tuple)) and isinstance(outputs, (list, tuple)) and
                 self._io_ok(inputs, outputs)):
             self.check_io(inputs, outputs)
-        B.plan_run_ptrs(self.handle, [x.data_ptr() for x in inputs], [y.data_ptr() for y in outputs],
-                        _stream_handle(stream))
+        B.plan_run_ptrs(self.handle, self.n_inputs, self.n_outputs, [x.data_ptr() for x in inputs],
+                        [y.data_ptr() for y in outputs], _stream_handle(stream))
         return outputs
 
     def autotune(self, inputs, outputs=None, reps=5, stream=None):

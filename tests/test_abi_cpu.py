@@ -515,6 +515,40 @@ def test_io_counts_and_tensor_checks_before_any_pointer_is_passed():
         plan.close()
 
 
+@pytest.mark.parametrize("role", ["inputs", "outputs"])
+def test_run_refuses_iterables_that_yield_once(monkeypatch, role):
+    """A generator that the checks have read to its end has no pointers left:
+    the run is refused by count before the library, whose call has no length
+    arguments, reads past an array."""
+    import torch
+    g = workloads.NetBuilder(seed=0)
+    a, b = g.input(1, 8, 8, 16, 0.0, 1.0), g.input(1, 8, 8, 16, 0.0, 1.0)
+    s = g.add(a, b)
+    g.mark_output(s)
+    g.mark_output(g.conv(s, 16, 1))
+    plan = engine.Plan(g.graph("once"), bind=False)
+    calls = []
+
+    class Lib:
+        def mgi_plan_run(self, *args):
+            calls.append(args)
+            return B.MGI_OK
+
+    monkeypatch.setattr(B, "_lib", Lib())
+    monkeypatch.setattr(engine, "_stream_handle", lambda stream: 0)
+    monkeypatch.setattr(plan, "check_io", lambda inputs, outputs: (list(inputs), list(outputs)))
+    plan.bound = True
+    io = {"inputs": [torch.zeros(1)] * 2, "outputs": [torch.zeros(1)] * 2}
+    plan.run(**io)
+    assert len(calls) == 1
+    io[role] = iter(io[role])
+    with pytest.raises(ValueError, match="2 inputs and 2 outputs"):
+        plan.run(**io)
+    assert len(calls) == 1
+    monkeypatch.undo()
+    plan.close()
+
+
 def test_read_node_raw_sizes_and_errors():
     """mgi_plan_read_node_raw: the stored size of a sliced node output can be
     queried without a run; fp32 outputs are refused; a copy needs
