@@ -1385,8 +1385,9 @@ mgi_status Lowering::bind_outputs() {
 // First and last node of every buffer (the lifetimes the planner shares
 // memory by, Sec. 5).
 void compute_lifetimes(mgi_plan &p) {
+    for (Buf &b : p.bufs) b.producer = b.last_use = -1;
     for (size_t i = 0; i < p.nodes.size(); ++i) {
-        Node &nd = p.nodes[i];
+        const Node &nd = p.nodes[i];
         p.bufs[nd.out].producer = (int)i;
         for (int b : nd.in) p.bufs[b].last_use = (int)i;
         if (nd.residual >= 0) p.bufs[nd.residual].last_use = (int)i;
@@ -1404,26 +1405,40 @@ void compute_lifetimes(mgi_plan &p) {
 
 }
 
-// Offsets of the arena buffers (the planner the options name, Sec. 5), then
-// the state region behind the arena.
-void plan_memory(mgi_plan &p, const mgi_options &o) {
-    std::vector<int> arena;
+// The arena buffers' sizes and shared objects (the planner the options name,
+// Sec. 5).  Views lie inside the tensor they are part of.
+struct ArenaPlan {
+    std::vector<int> bufs;
     std::vector<size_t> sizes;
+    PlanResult objects;
+    size_t bytes = 0;        // objects at 256-byte offsets, one after the other
+};
+
+ArenaPlan plan_arena(const mgi_plan &p, const mgi_options &o) {
+    ArenaPlan a;
     std::vector<int> first, last;
     for (size_t b = 0; b < p.bufs.size(); ++b) {
         if (p.bufs[b].loc != Loc::Arena || p.bufs[b].dead || p.bufs[b].view_of >= 0) continue;
-        arena.push_back((int)b);
-        sizes.push_back(p.bufs[b].bytes);
+        a.bufs.push_back((int)b);
+        a.sizes.push_back(p.bufs[b].bytes);
         first.push_back(p.bufs[b].producer);
         last.push_back(p.bufs[b].last_use);
     }
-    PlanResult naive = plan_naive(sizes);
-    PlanResult pr = o.materialize_all                   ? naive
-                    : o.planner == MGI_PLANNER_GREEDY ? plan_greedy(sizes, first, last)
-                    : o.planner == MGI_PLANNER_MCFP   ? plan_mcfp(sizes, first, last)
-                                                      : naive;
+    a.objects = o.materialize_all                   ? plan_naive(a.sizes)
+                : o.planner == MGI_PLANNER_GREEDY ? plan_greedy(a.sizes, first, last)
+                : o.planner == MGI_PLANNER_MCFP   ? plan_mcfp(a.sizes, first, last)
+                                                  : plan_naive(a.sizes);
+    for (size_t s : a.objects.object_size) a.bytes = align256(a.bytes + s);
+    return a;
+}
+
+// Offsets of the arena buffers, then the state region behind the arena.
+void plan_memory(mgi_plan &p, const mgi_options &o) {
+    const ArenaPlan a = plan_arena(p, o);
+    const std::vector<int> &arena = a.bufs;
+    const PlanResult &pr = a.objects;
     p.mem_naive = 0;
-    for (size_t s : sizes) p.mem_naive += s;
+    for (size_t s : a.sizes) p.mem_naive += s;
     p.mem_planned = 0;
     std::vector<size_t> obj_off(pr.object_size.size());
     size_t off = 0;
@@ -1588,34 +1603,65 @@ void absorb_exports(mgi_plan &p) {
     }
 }
 
+// Makes the operands of a concatenation views of its output, if they can be.
+bool alias_concat(mgi_plan &p, Node &cc, const std::vector<int> &producer, std::vector<char> &parent) {
+    if (p.bufs[cc.out].loc != Loc::Arena || p.bufs[cc.out].view_of >= 0) return false;
+    for (size_t k = 0; k < cc.in.size(); ++k) {
+        const Buf &b = p.bufs[cc.in[k]];
+        if (b.layout != Layout::C8 || b.loc != Loc::Arena || b.dead || b.view_of >= 0 || parent[cc.in[k]] ||
+            producer[cc.in[k]] < 0 || (b.shape.c % 8 != 0 && k + 1 < cc.in.size()) ||
+            std::count(cc.in.begin(), cc.in.end(), cc.in[k]) != 1)
+            return false;
+    }
+    int slice = 0;
+    for (int b : cc.in) {
+        p.bufs[b].view_of = cc.out;
+        p.bufs[b].view_slice = slice;
+        slice += slices(p.bufs[b].shape.c);
+    }
+    parent[cc.out] = 1;
+    cc.absorbed = true;
+    return true;
+}
+
+void unalias_concat(mgi_plan &p, Node &cc, std::vector<char> &parent) {
+    for (int b : cc.in) p.bufs[b].view_of = -1;
+    parent[cc.out] = 0;
+    cc.absorbed = false;
+}
+
 // Concatenation without a copy: slices are the slowest index of a sliced
 // tensor, so an operand in whole slices is a contiguous part of the
 // concatenated tensor, and its producer can write it there (the concat node
 // stays in the list and launches nothing).  Where every operand but the last
 // is in whole slices, and each is an intermediate tensor of its own.  Not with
 // materialize_all.
-void alias_concats(mgi_plan &p) {
+// The concatenated tensor then lives from its first operand on.  Where large
+// tensors come and go before its last operand that can take more memory than
+// the copy does, and a plan must not outgrow its workspace for it: such
+// concatenations keep the copy (all of them at once need more: one by one, in
+// order, those that do not).
+void alias_concats(mgi_plan &p, const mgi_options &o) {
     std::vector<int> producer(p.bufs.size(), -1);
     for (size_t i = 0; i < p.nodes.size(); ++i) producer[p.nodes[i].out] = (int)i;
     std::vector<char> parent(p.bufs.size(), 0);
-    for (Node &cc : p.nodes) {
-        if (cc.kind != NodeKind::Concat || p.bufs[cc.out].loc != Loc::Arena || p.bufs[cc.out].view_of >= 0) continue;
-        bool ok = true;
-        for (size_t k = 0; k < cc.in.size(); ++k) {
-            const Buf &b = p.bufs[cc.in[k]];
-            ok = ok && b.layout == Layout::C8 && b.loc == Loc::Arena && !b.dead && b.view_of < 0 && !parent[cc.in[k]] &&
-                 producer[cc.in[k]] >= 0 && (b.shape.c % 8 == 0 || k + 1 == cc.in.size()) &&
-                 std::count(cc.in.begin(), cc.in.end(), cc.in[k]) == 1;
-        }
-        if (!ok) continue;
-        int slice = 0;
-        for (int b : cc.in) {
-            p.bufs[b].view_of = cc.out;
-            p.bufs[b].view_slice = slice;
-            slice += slices(p.bufs[b].shape.c);
-        }
-        parent[cc.out] = 1;
-        cc.absorbed = true;
+    auto arena_bytes = [&]() {
+        compute_lifetimes(p);
+        return plan_arena(p, o).bytes;
+    };
+    std::vector<Node *> done;
+    for (Node &nd : p.nodes)
+        if (nd.kind == NodeKind::Concat && alias_concat(p, nd, producer, parent)) done.push_back(&nd);
+    if (done.empty()) return;
+    const size_t with = arena_bytes();
+    for (Node *cc : done) unalias_concat(p, *cc, parent);
+    size_t bytes = arena_bytes();
+    const bool all = with <= bytes;
+    for (Node &nd : p.nodes) {
+        if (nd.kind != NodeKind::Concat || !alias_concat(p, nd, producer, parent) || all) continue;
+        const size_t b = arena_bytes();
+        if (b <= bytes) bytes = b;
+        else unalias_concat(p, nd, parent);
     }
 }
 
@@ -1677,7 +1723,7 @@ mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p
     if (o.fuse && o.fuse_softmax) fuse_softmax_into_fc(p);
     if (o.fuse && o.fuse_dwpw) fuse_dw_into_pw(p);
     if (o.fuse && !o.materialize_all) {
-        alias_concats(p);
+        alias_concats(p, o);
         absorb_exports(p);
         absorb_ingests(p, o);
     }

@@ -549,6 +549,50 @@ def test_run_refuses_iterables_that_yield_once(monkeypatch, role):
     plan.close()
 
 
+def concat_net(widths):
+    """x -> a (8 channels); x -> wide layers -> b; concat(a, b) -> output.
+    Returns the description and the sliced tensors as (channels, first node,
+    last node) by the node order ingest, a, wide .., b, concat, output, export."""
+    g = workloads.NetBuilder(seed=0)
+    x = g.input(1, 8, 8, 8, 0.0, 1.0)
+    a = g.conv(x, 8, 1)
+    t, live = x, [[8, 0, 2], [8, 1, len(widths) + 3]]
+    for k, c in enumerate(widths):
+        t = g.conv(t, c, 1)
+        live.append([c, 2 + k, 3 + k])
+    b = g.conv(t, 256, 1)
+    nd = len(widths) + 2
+    live += [[256, nd, nd + 1], [264, nd + 1, nd + 2], [24, nd + 2, nd + 3]]
+    g.mark_output(g.conv(g.concat([a, b]), 24, 1))
+    return g.graph("concat memory"), live
+
+
+@pytest.mark.parametrize("planner", [B.PLANNER_GREEDY, B.PLANNER_MCFP])
+@pytest.mark.parametrize("widths,views", [((512, 512), False), ((), True)])
+def test_concat_views_need_no_more_memory_than_the_copy(planner, widths, views):
+    """A concatenation written in place lives from its first operand on.  Where
+    that would make the arena larger than with a copy (two wide layers between
+    the operands), the copy stays; where it does not, the operands need no
+    memory of their own."""
+    desc, live = concat_net(widths)
+    plan = engine.Plan(desc, bind=False, planner=planner)
+    assert [k["kind"] for k in plan.nodes()].count("concat") == 1
+    sizes = [c * 64 * 2 for c, _, _ in live]
+    first, last = [f for _, f, _ in live], [t for _, _, t in live]
+    _, copied = B.mgi_planner_assign(planner, sizes, first, last)
+    planned = plan.memory_report()[1]
+    if not views:
+        assert planned == sum(copied)
+    else:
+        operands = [k for k, (c, _, t) in enumerate(live) if t == len(widths) + 3 and c in (8, 256)]
+        keep = [k for k in range(len(live)) if k not in operands]
+        whole = next(k for k in keep if live[k][0] == 264)
+        first[whole] = min(first[k] for k in operands)
+        _, viewed = B.mgi_planner_assign(planner, [sizes[k] for k in keep], [first[k] for k in keep], [last[k] for k in keep])
+        assert planned == sum(viewed) < sum(copied)
+    plan.close()
+
+
 def test_read_node_raw_sizes_and_errors():
     """mgi_plan_read_node_raw: the stored size of a sliced node output can be
     queried without a run; fp32 outputs are refused; a copy needs
