@@ -1437,8 +1437,10 @@ void plan_memory(mgi_plan &p, const mgi_options &o) {
     const ArenaPlan a = plan_arena(p, o);
     const std::vector<int> &arena = a.bufs;
     const PlanResult &pr = a.objects;
+    // (one buffer per tensor: views count as the tensors they are)
     p.mem_naive = 0;
-    for (size_t s : a.sizes) p.mem_naive += s;
+    for (const Buf &b : p.bufs)
+        if (b.loc == Loc::Arena && !b.dead) p.mem_naive += b.bytes;
     p.mem_planned = 0;
     std::vector<size_t> obj_off(pr.object_size.size());
     size_t off = 0;
