@@ -190,15 +190,19 @@ void add_gemm_configs(Node &nd, size_t M) {
             }
         }
     }
-    if (nd.taps && nd.tile.pipe) return;     // (the staged kernel: 44 us where the ring takes 15)
+    // The LDS-staged kernel: of a windowed convolution in the ring only the
+    // tile it would pick (3x3, 4 x 33 x 33 x 256 -> 256: 44 us where the ring
+    // takes 15), which also keeps every configuration number that a stored
+    // tuning may hold from before these nodes had other first choices.
     const int ldss[5][2] = {{128, 128}, {64, 128}, {32, 128}, {64, 64}, {128, 64}};
     for (auto &lb : ldss) {
-        if (lb[1] > 64 && npad <= 64) continue;
+        if ((lb[1] > 64 && npad <= 64) || (nd.taps && nd.tile.pipe)) continue;
         GemmTile t;
         t.bm = lb[0];
         t.bn = lb[1];
         push(t);
     }
+    push(pick_tile(M, nd.conv.cout));
 }
 
 // Output rows per thread of the 3x3 depthwise kernel: four at stride 1, two at

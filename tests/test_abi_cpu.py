@@ -594,6 +594,25 @@ def test_concat_views_need_no_more_memory_than_the_copy(planner, widths, views):
     plan.close()
 
 
+@pytest.mark.parametrize("n,hw,cin,cout,k,count", [(4, 33, 256, 256, 3, 5), (1, 7, 32, 24, 3, 3), (2, 14, 512, 512, 1, 9)])
+def test_gemm_configuration_numbers_stay_valid(n, hw, cin, cout, k, count):
+    """A stored tuning is a list of configuration numbers: every number that a
+    pointwise or windowed convolution's list has had is still accepted."""
+    g = workloads.NetBuilder(seed=0)
+    t = g.conv(g.input(n, hw, hw, cin, 0.0, 1.0), cout, k)
+    g.mark_output(t)
+    plan = engine.Plan(g.graph("numbers"), bind=False)
+    node = [i for i, k in enumerate(plan.nodes()) if k["kind"] in ("pw_gemm", "conv_igemm")][0]
+    assert plan.node_configs()[node][1] >= count
+    names = []
+    for c in range(plan.node_configs()[node][1]):
+        B.mgi_plan_set_node_config(plan.handle, node, c)
+        names.append(plan.node_configs()[node][2])
+    assert len(set(names)) == len(names)
+    assert names[-1].startswith("lds")
+    plan.close()
+
+
 def test_read_node_raw_sizes_and_errors():
     """mgi_plan_read_node_raw: the stored size of a sliced node output can be
     queried without a run; fp32 outputs are refused; a copy needs
