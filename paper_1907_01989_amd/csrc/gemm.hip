@@ -743,16 +743,30 @@ static hipError_t launch_pipe_t(const GemmParams &p, hipStream_t st) {
 
 static unsigned inv31(int d) { return (unsigned)((0x80000000ull + d - 1) / d); }
 
-bool conv_pipe_ok(int kh, int kw, int ksp, int H, int W, int OH, int OW) {
-    // 32-bit byte offsets over the images a 128-row tile touches, and its
-    // window origins
-    const uint64_t imgs = 128 / ((uint64_t)OH * OW) + 3;
-    return (int64_t)kh * kw <= kMaxTaps && ksp < 32768 && imgs * H * W < (1ull << 26);
+// Input pixels between the lowest and the highest address that a 128-row tile
+// of the ring kernel forms, inside the input or not: the images the tile
+// touches, and the padded plane that window origins and taps range over.
+static uint64_t conv_span(const ConvGeom &g) {
+    const uint64_t imgs = 128 / ((uint64_t)g.OH * g.OW) + 3;
+    const uint64_t rows = (uint64_t)g.pt + (uint64_t)(g.OH - 1) * g.sh + (uint64_t)(g.kh - 1) * g.dh + 1;
+    const uint64_t cols = (uint64_t)g.pl + (uint64_t)(g.OW - 1) * g.sw + (uint64_t)(g.kw - 1) * g.dw + 1;
+    const uint64_t lim = 1ull << 31;
+    if (rows >= lim || cols >= lim) return ~0ull;                // (products below stay under 2^63)
+    return (imgs * g.H + rows) * g.W + cols;
 }
 
-bool conv_nhwc_ok(int sin, int ks, int H, int W, int OH, int OW) {
-    const uint64_t imgs = 128 / ((uint64_t)OH * OW) + 3;
-    return sin % ks == 0 && imgs * H * W * sin < (1ull << 27);
+bool conv_pipe_ok(const ConvGeom &g, int ksp) {
+    // 32-bit byte offsets
+    return (int64_t)g.kh * g.kw <= kMaxTaps && ksp < 32768 && conv_span(g) < (1ull << 26);
+}
+
+bool conv_nhwc_ok(const ConvGeom &g, int sin, int ks) {
+    const uint64_t span = conv_span(g);
+    return sin % ks == 0 && span < (1ull << 27) && span * sin < (1ull << 27);
+}
+
+static ConvGeom conv_geom(const GemmParams &p) {
+    return {p.H, p.W, p.OH, p.OW, p.kh, p.kw, p.sh, p.sw, p.dh, p.dw, p.pt, p.pl};
 }
 
 template <typename E, int BM, int BN, int KS>
@@ -762,7 +776,7 @@ static hipError_t launch_conv_t(const GemmParams &p, hipStream_t st) {
     q.ntiles = (p.nb16 * 16 + BN - 1) / BN;
     q.inv_sin = inv31(p.sin);
     q.inv_kw = inv31(p.kw);
-    if (p.xp != 1 && !conv_nhwc_ok(p.sin, KS, p.H, p.W, p.OH, p.OW)) return hipErrorInvalidValue;
+    if (p.xp != 1 && !conv_nhwc_ok(conv_geom(p), p.sin, KS)) return hipErrorInvalidValue;
     if (p.sin % KS == 0) return launch_ring<E, BM, BN, false, KS, 2>(q, st);
     return launch_ring<E, BM, BN, false, KS, 1>(q, st);
 }
@@ -779,7 +793,7 @@ static hipError_t launch_conv_e(const GemmParams &p, int bm, int bn, int ks, hip
 hipError_t launch_gemm_conv(const GemmParams &p, int bm, int bn, int ks, hipStream_t st) {
     if (p.M <= 0) return hipSuccess;
     if (!p.taps || !p.zero || p.sin < 1 || p.kh < 1 || p.kw < 1 || p.ksp % 8 != 0 || p.ksl != p.kh * p.kw * p.sin ||
-        !conv_pipe_ok(p.kh, p.kw, p.ksp, p.H, p.W, p.OH, p.OW))
+        !conv_pipe_ok(conv_geom(p), p.ksp))
         return hipErrorInvalidValue;
     return p.bf16 ? launch_conv_e<BF16>(p, bm, bn, ks, st) : launch_conv_e<F16>(p, bm, bn, ks, st);
 }

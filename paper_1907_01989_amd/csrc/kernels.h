@@ -85,9 +85,14 @@ hipError_t launch_gemm_pipe_k8(const GemmParams &p, bool pool, hipStream_t st);
 // shapes it covers (windows of at most kMaxTaps taps, offsets in range).
 constexpr int kMaxTaps = 31;
 constexpr int kConvTiles[4][3] = {{64, 64, 4}, {64, 32, 8}, {128, 32, 8}, {64, 128, 4}};
+// Window geometry of a convolution (planes, window, strides, dilations, top
+// and left padding).
+struct ConvGeom {
+    int H, W, OH, OW, kh, kw, sh, sw, dh, dw, pt, pl;
+};
 // conv_nhwc_ok: ... and with an input of sin slices read as NHWC.
-bool conv_pipe_ok(int kh, int kw, int ksp, int H, int W, int OH, int OW);
-bool conv_nhwc_ok(int sin, int ks, int H, int W, int OH, int OW);
+bool conv_pipe_ok(const ConvGeom &g, int ksp);
+bool conv_nhwc_ok(const ConvGeom &g, int sin, int ks);
 hipError_t launch_gemm_conv(const GemmParams &p, int bm, int bn, int ks, hipStream_t st);
 // pointwise GEMM whose output feeds only a global average pool: M-tiles of
 // bm rows hold bm / hw whole images (hw <= 64 pixels each, M = nimg * hw),

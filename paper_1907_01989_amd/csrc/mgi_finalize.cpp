@@ -1147,8 +1147,7 @@ mgi_status Lowering::lower_conv(const Group &G, const GOp &op, const Shape &out_
     }
     nd.nb16 = (d.cout + 15) / 16;
     nd.tile = pick_tile(out_shape.pixels(), d.cout);
-    if (nd.kind == NodeKind::Gemm && nd.taps && nd.ksp % 8 == 0 &&
-        kern::conv_pipe_ok(d.kh, d.kw, nd.ksp, x.h, x.w, out_shape.h, out_shape.w)) {
+    if (nd.kind == NodeKind::Gemm && nd.taps && nd.ksp % 8 == 0 && kern::conv_pipe_ok(conv_geom(d, x, out_shape), nd.ksp)) {
         nd.tile = pick_conv_tile(out_shape.pixels(), nd.nb16 * 16);
     } else if (nd.kind == NodeKind::Gemm && !nd.taps) {
         nd.tile = pick_pw_tile(out_shape.pixels(), nd.nb16 * 16, nd.ksl, nd.ksp);

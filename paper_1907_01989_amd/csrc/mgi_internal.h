@@ -260,6 +260,10 @@ PlanResult plan_mcfp(const std::vector<size_t> &sizes, const std::vector<int> &f
 // finalize steps
 mgi_status build_plan(const mgi_graph &g, const mgi_options &o, mgi_plan &p);
 
+inline kern::ConvGeom conv_geom(const mgi_conv_desc &d, const Shape &x, const Shape &y) {
+    return {x.h, x.w, y.h, y.w, d.kh, d.kw, d.stride_h, d.stride_w, d.dil_h, d.dil_w, d.pad_t, d.pad_l};
+}
+
 namespace kern {
 struct StemDwParams;
 }

@@ -63,7 +63,7 @@ void *buf_ptr(const mgi_plan &p, int b, const Bases &B) {
 bool reads_in_place(const mgi_plan &p, const Node &nd) {
     if (nd.kind != NodeKind::Gemm || !nd.taps || !nd.tile.pipe) return true;
     const Shape &x = p.bufs[nd.in[0]].shape, &y = p.bufs[nd.out].shape;
-    return conv_nhwc_ok((x.c + 7) / 8, nd.tile.ks, x.h, x.w, y.h, y.w);
+    return conv_nhwc_ok(conv_geom(nd.conv, x, y), (x.c + 7) / 8, nd.tile.ks);
 }
 
 // The graph inputs that a run's kernels read in place, one bit per absorbed

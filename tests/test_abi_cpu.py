@@ -613,6 +613,37 @@ def test_gemm_configuration_numbers_stay_valid(n, hw, cin, cout, k, count):
     plan.close()
 
 
+@pytest.mark.parametrize("h,w,pads,dil,ring", [
+    (33, 33, (1, 1, 1, 1), (1, 1), True),
+    (33, 33, (200, 200, 200, 200), (1, 1), True),
+    (4, 4096, (70000, 70000, 1, 1), (1, 1), False),        # window origins past 2^28 pixels
+    (4, 4096, (524287, 524289, 1, 1), (524288, 1), False),  # a tap 2^31 pixels below its origin
+    (1, 4, (1, 1, 70000000, 70000000), (1, 70000000), False),
+])
+def test_window_ring_needs_its_offsets_in_range(h, w, pads, dil, ring):
+    """The ring kernel forms 32-bit offsets over the padded plane: padding and
+    dilation past their range keep the kernel with 64-bit addresses."""
+    g = B.mgi_graph_create()
+    try:
+        x = B.mgi_graph_add_input(g, 1, h, w, 8, B.DTYPE_FP16)
+        desc = B.conv_desc(3, 3, dil=dil, pads=pads, cout=16)
+        y = B.mgi_graph_add_conv2d(g, x, desc, np.zeros((16, 3, 3, 8), np.float32), np.zeros(16, np.float32))
+        B.mgi_graph_mark_output(g, y)
+        p = B.mgi_graph_finalize(g)
+        try:
+            kinds = [B.mgi_plan_node_info(p, i)["kind"] for i in range(B.mgi_plan_node_count(p))]
+            node = kinds.index("conv_igemm")
+            names = []
+            for c in range(B.mgi_plan_node_config(p, node)[1]):
+                B.mgi_plan_set_node_config(p, node, c)
+                names.append(B.mgi_plan_node_config(p, node)[2])
+            assert any(k.startswith("pipe") for k in names) == ring, names
+        finally:
+            B.mgi_plan_destroy(p)
+    finally:
+        B.mgi_graph_destroy(g)
+
+
 def test_read_node_raw_sizes_and_errors():
     """mgi_plan_read_node_raw: the stored size of a sliced node output can be
     queried without a run; fp32 outputs are refused; a copy needs
