@@ -480,9 +480,12 @@ __device__ __forceinline__ void store_tile_c8(const GemmParams &p, const f4 (&ac
 // workgroup, 10.6 and 9.3).
 // The standalone softmax kernel and the FC kernel's fused softmax both use it,
 // so the two forms round alike, for any PER that holds the row.
+// (Inlined always: as calls they gave the FC kernel the registers of the largest
+// of them, 262 instead of 132, and a jump to code not yet fetched; one row of
+// 1000 classes 0.08 us.)
 constexpr int kSoftmaxRegCols = 64 * 16;
 template <int PER, int U>
-__device__ inline void softmax_regs(const float *z, float *y, int r0, int rs, int rows, int cols, int lane) {
+__device__ __forceinline__ void softmax_regs(const float *z, float *y, int r0, int rs, int rows, int cols, int lane) {
     float v[U][PER], m[U], s[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -533,7 +536,7 @@ __device__ inline void softmax_regs(const float *z, float *y, int r0, int rs, in
 }
 // the same for the fewest registers that hold the row
 template <int U>
-__device__ inline void softmax_rows(const float *z, float *y, int r0, int rs, int rows, int cols, int lane) {
+__device__ __forceinline__ void softmax_rows(const float *z, float *y, int r0, int rs, int rows, int cols, int lane) {
     if (cols <= 64 * 2) softmax_regs<2, U>(z, y, r0, rs, rows, cols, lane);
     else if (cols <= 64 * 6) softmax_regs<6, U>(z, y, r0, rs, rows, cols, lane);
     else softmax_regs<16, U>(z, y, r0, rs, rows, cols, lane);
