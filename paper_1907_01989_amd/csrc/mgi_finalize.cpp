@@ -909,6 +909,29 @@ std::vector<char> live_ops(const mgi_graph &g) {
 }
 
 
+// A windowed convolution whose 8-slice tile alone would keep a graph input from
+// being read in place (input slices not a multiple of 8) takes the 4-slice one
+// where that can: the narrower tile saves less than the conversion kernel costs
+// (3x3 on fp16 graph inputs, whole run: 33 x 33 x 96 -> 96 9.1 us with 64 x 32
+// tiles and the conversion, 7.3 with 64 x 64 ones; 16 x 56 x 56 x 96 -> 24 21.4
+// and 13.0; 33 x 33 x 352 -> 128 16.4 and 14.5).
+void keep_inputs_in_place(mgi_plan &p) {
+    for (const Node &in : p.nodes) {
+        std::vector<std::pair<int, GemmTile>> changed;
+        bool all = true;
+        for (int r : in.direct_readers) {
+            Node &nd = p.nodes[r];
+            if (reads_in_place(p, nd)) continue;
+            changed.push_back({r, nd.tile});
+            nd.tile = GemmTile{};
+            nd.tile.pipe = true;
+            all = all && reads_in_place(p, nd);
+        }
+        if (all) continue;
+        for (auto &c : changed) p.nodes[c.first].tile = c.second;
+    }
+}
+
 mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p);
 
 }  // namespace
@@ -1731,6 +1754,7 @@ mgi_status build_plan_impl(const mgi_graph &g, const mgi_options &o, mgi_plan &p
         alias_concats(p, o);
         absorb_exports(p);
         absorb_ingests(p, o);
+        keep_inputs_in_place(p);
     }
     for (Node &nd : p.nodes) add_configs(p, nd, p.bufs[nd.out].shape.pixels());
     compute_lifetimes(p);

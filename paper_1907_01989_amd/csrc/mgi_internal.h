@@ -264,6 +264,15 @@ inline kern::ConvGeom conv_geom(const mgi_conv_desc &d, const Shape &x, const Sh
     return {x.h, x.w, y.h, y.w, d.kh, d.kw, d.stride_h, d.stride_w, d.dil_h, d.dil_w, d.pad_t, d.pad_l};
 }
 
+// Whether node nd, in its configuration, can read an input in place (a window
+// GEMM's ring walks whole taps per stage; every other kernel of the kinds
+// absorb_ingests lists can).
+inline bool reads_in_place(const mgi_plan &p, const Node &nd) {
+    if (nd.kind != NodeKind::Gemm || !nd.taps || !nd.tile.pipe) return true;
+    const Shape &x = p.bufs[nd.in[0]].shape;
+    return kern::conv_nhwc_ok(conv_geom(nd.conv, x, p.bufs[nd.out].shape), (x.c + 7) / 8, nd.tile.ks);
+}
+
 namespace kern {
 struct StemDwParams;
 }

@@ -57,15 +57,6 @@ void *buf_ptr(const mgi_plan &p, int b, const Bases &B) {
     return nullptr;
 }
 
-// Whether node nd, in its configuration, can read an input in place (a window
-// GEMM's ring walks whole taps per stage; every other kernel of the kinds
-// absorb_ingests lists can).
-bool reads_in_place(const mgi_plan &p, const Node &nd) {
-    if (nd.kind != NodeKind::Gemm || !nd.taps || !nd.tile.pipe) return true;
-    const Shape &x = p.bufs[nd.in[0]].shape, &y = p.bufs[nd.out].shape;
-    return conv_nhwc_ok(conv_geom(nd.conv, x, y), (x.c + 7) / 8, nd.tile.ks);
-}
-
 // The graph inputs that a run's kernels read in place, one bit per absorbed
 // ingest node: none where outputs overlap inputs, and not an array off a
 // 16-byte boundary.

@@ -644,6 +644,26 @@ def test_window_ring_needs_its_offsets_in_range(h, w, pads, dil, ring):
         B.mgi_graph_destroy(g)
 
 
+@pytest.mark.parametrize("n,hw,cin,cout,k,src,dtype,first", [
+    (1, 33, 96, 96, 3, B.DTYPE_FP16, B.DTYPE_FP16, "pipe64x64"),      # 12 slices: read in place by 4-slice stages only
+    (16, 56, 96, 24, 3, B.DTYPE_FP16, B.DTYPE_FP16, "pipe64x64"),
+    (1, 56, 32, 32, 5, B.DTYPE_FP16, B.DTYPE_FP16, "pipe64x64"),
+    (1, 33, 128, 96, 3, B.DTYPE_FP16, B.DTYPE_FP16, "pipe64x32k8"),   # 16 slices: by either
+    (1, 33, 48, 96, 3, B.DTYPE_FP16, B.DTYPE_FP16, "pipe64x32k8"),    # 6 slices: by neither
+    (1, 33, 96, 96, 3, B.DTYPE_FP32, B.DTYPE_FP16, "pipe64x32k8"),    # converted inputs
+    (1, 33, 96, 96, 3, B.DTYPE_FP16, B.DTYPE_BF16, "pipe64x32k8"),
+])
+def test_window_tile_keeps_the_input_in_place(n, hw, cin, cout, k, src, dtype, first):
+    """The default tile of a windowed convolution on a graph input is one that
+    reads it in place, where one can."""
+    g = workloads.NetBuilder(seed=0)
+    g.mark_output(g.conv(g.input(n, hw, hw, cin, 0.0, 1.0, dtype=src), cout, k))
+    plan = engine.Plan(g.graph("window"), bind=False, dtype=dtype)
+    node = [i for i, k in enumerate(plan.nodes()) if k["kind"] == "conv_igemm"][0]
+    assert plan.node_configs()[node][2] == first
+    plan.close()
+
+
 def test_read_node_raw_sizes_and_errors():
     """mgi_plan_read_node_raw: the stored size of a sliced node output can be
     queried without a run; fp32 outputs are refused; a copy needs
