@@ -344,7 +344,9 @@ mgi_status mgi_plan_read_node_raw(mgi_plan *p, int i, void *dev_dst, size_t *byt
  * (pointwise / implicit-GEMM, depthwise, fused pointwise -> depthwise) inside
  * `reps` whole runs of the plan, queued back to back (plus one warm-up run;
  * only the node's kernels are timestamped, so it meets its input as in a
- * run), and keeps the one with the lowest median time (a candidate listed
+ * run; a candidate that alone keeps a graph input from being read in place
+ * counts the conversion kernel too), and keeps the one with the lowest
+ * median time (a candidate listed
  * later replaces an earlier one only when more than 2% faster; fused forms
  * are listed before split ones).  All candidates produce bit-identical
  * results.  Synchronises `stream` once per candidate; releases a captured

@@ -57,18 +57,22 @@ void *buf_ptr(const mgi_plan &p, int b, const Bases &B) {
     return nullptr;
 }
 
+// Whether the readers of ingest node nd's output, but for node `except`, read
+// the input in place in this run: not where outputs overlap inputs, and not an
+// array off a 16-byte boundary.
+bool read_in_place(const mgi_plan &p, const Node &nd, const Bases &B, int except = -1) {
+    if (!B.direct || nd.direct_readers.empty() || ((uintptr_t)buf_ptr(p, nd.in[0], B) & 15) != 0) return false;
+    for (int r : nd.direct_readers)
+        if (r != except && !reads_in_place(p, p.nodes[r])) return false;
+    return true;
+}
+
 // The graph inputs that a run's kernels read in place, one bit per absorbed
-// ingest node: none where outputs overlap inputs, and not an array off a
-// 16-byte boundary.
+// ingest node.
 uint64_t inputs_in_place(const mgi_plan &p, const Bases &B) {
     uint64_t mask = 0;
-    if (!B.direct) return mask;
-    for (const Node &nd : p.nodes) {
-        if (nd.direct_readers.empty()) continue;
-        bool ok = ((uintptr_t)buf_ptr(p, nd.in[0], B) & 15) == 0;
-        for (int r : nd.direct_readers) ok = ok && reads_in_place(p, p.nodes[r]);
-        if (ok) mask |= 1ull << p.bufs[nd.out].direct_bit;
-    }
+    for (const Node &nd : p.nodes)
+        if (!nd.direct_readers.empty() && read_in_place(p, nd, B)) mask |= 1ull << p.bufs[nd.out].direct_bit;
     return mask;
 }
 
@@ -840,7 +844,8 @@ extern "C" mgi_status mgi_plan_replay(mgi_plan *p, void *stream) {
 // configuration is launched reps + 1 times per candidate on the plan's own
 // buffers (after one full run has filled them), each launch timestamped on the
 // device; the one with the lowest median over the timed launches (the first
-// launch being a warm-up) is kept, a later candidate replacing an earlier one
+// launch being a warm-up; the conversion of an input that this candidate alone
+// keeps from being read in place counts with it) is kept, a later candidate replacing an earlier one
 // only when more than 2% faster.  Candidates compute identical results, so tuning changes
 // speed only.  A captured graph holds the old configurations and is released.
 extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inputs,
@@ -853,8 +858,12 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
     release_graph(*p);
     hipStream_t st = static_cast<hipStream_t>(stream);
     // one start/stop pair per run, so that a candidate's runs go back to
-    // back (as in steady operation) and are read after one synchronisation
-    std::vector<hipEvent_t> evs(2 * (size_t)(reps + 1), nullptr);
+    // back (as in steady operation) and are read after one synchronisation; a
+    // window GEMM's runs have pairs for the conversions of its operands too
+    size_t pairs = 1;
+    for (const Node &nd : p->nodes)
+        if (nd.kind == NodeKind::Gemm && nd.taps) pairs = 3;
+    std::vector<hipEvent_t> evs(2 * pairs * (size_t)(reps + 1), nullptr);
     hipError_t e = hipSuccess;
     for (size_t k = 0; k < evs.size() && e == hipSuccess; ++k) e = hipEventCreate(&evs[k]);
     auto destroy = [&]() {
@@ -878,14 +887,24 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
         for (size_t c = 0; c < nd.cfgs.size() && result == MGI_OK; ++c) {
             nd.apply((int)c);
             B.in_place = inputs_in_place(*p, B);
+            // the nodes whose time counts: this one, and an ingest that would
+            // not be launched but for it
+            std::vector<size_t> timed{ni};
+            for (size_t j = 0; j < p->nodes.size(); ++j) {
+                const Node &in = p->nodes[j];
+                if (!reads_in_place(*p, nd) && std::count(in.direct_readers.begin(), in.direct_readers.end(), (int)ni) &&
+                    read_in_place(*p, in, B, (int)ni) && timed.size() < pairs)
+                    timed.push_back(j);
+            }
             bool usable = true;
             for (int r = 0; r <= reps && usable && result == MGI_OK; ++r) {
                 // the whole plan runs, so that the node meets its input as it
                 // does in a run (just written by its producer), and only the
-                // node's kernels are timestamped
+                // kernels that count are timestamped
                 for (size_t j = 0; j < p->nodes.size(); ++j) {
-                    ev.start = j == ni ? evs[2 * r] : nullptr;
-                    ev.stop = j == ni ? evs[2 * r + 1] : nullptr;
+                    const size_t k = std::find(timed.begin(), timed.end(), j) - timed.begin();
+                    ev.start = k < timed.size() ? evs[2 * (pairs * r + k)] : nullptr;
+                    ev.stop = k < timed.size() ? evs[2 * (pairs * r + k) + 1] : nullptr;
                     e = launch_node(*p, p->nodes[j], B, st);
                     ev.start = ev.stop = nullptr;
                     if (e == hipSuccess) continue;
@@ -905,9 +924,13 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
             if (!usable) continue;
             times.clear();
             for (int r = 1; r <= reps && e == hipSuccess; ++r) {
-                float ms = 0.0f;
-                e = hipEventElapsedTime(&ms, evs[2 * r], evs[2 * r + 1]);
-                times.push_back(ms);
+                float sum = 0.0f;
+                for (size_t k = 0; k < timed.size() && e == hipSuccess; ++k) {
+                    float ms = 0.0f;
+                    e = hipEventElapsedTime(&ms, evs[2 * (pairs * r + k)], evs[2 * (pairs * r + k) + 1]);
+                    sum += ms;
+                }
+                times.push_back(sum);
             }
             if (e != hipSuccess) {
                 result = hip_fail(e, "mgi_plan_autotune: timing");

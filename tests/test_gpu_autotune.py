@@ -65,3 +65,28 @@ def test_autotuned_plan_reproduces_default(net, batch):
     for g, r in zip(got, ref):
         np.testing.assert_array_equal(g, r)
     plan.close()
+
+
+def test_autotune_counts_the_conversion_a_tile_needs():
+    """A 5x5 convolution of a 32-channel fp16 input: the tile with 8-slice stages
+    is the faster kernel by a little, but cannot read the input in place, and
+    the conversion kernel it needs costs more."""
+    import torch
+    from paper_1907_01989_amd import engine
+    g = workloads.NetBuilder(seed=3)
+    g.mark_output(g.conv(g.input(1, 56, 56, 32, 0.0, 1.0, dtype=workloads.DTYPE_FP16), 32, 5))
+    log("[case] autotune conv 5x5 1x56x56x32")
+    plan = engine.Plan(g.graph("conversion"))
+    xs = plan.input_tensors()
+    ref = plan.run(xs)[0].cpu().numpy()
+    plan.autotune(xs, reps=10)
+    node = [i for i, k in enumerate(plan.nodes()) if k["kind"] == "conv_igemm"][0]
+    assert plan.node_configs()[node][2] == "pipe64x64"
+    np.testing.assert_array_equal(plan.run(xs)[0].cpu().numpy(), ref)
+    # an input off 16 bytes is converted whatever the tile: the faster kernel
+    buf = torch.empty(xs[0].numel() + 1, dtype=xs[0].dtype, device="cuda")
+    xo = buf[1:].view(xs[0].shape)
+    xo.copy_(xs[0])
+    plan.autotune([xo], reps=10)
+    np.testing.assert_array_equal(plan.run([xo])[0].cpu().numpy(), ref)
+    plan.close()
