@@ -173,3 +173,50 @@ def test_kernels_read_the_input_in_place(kind, n, h, w, c, cout):
                 for o, r in zip(outs, ref):
                     np.testing.assert_array_equal(o.cpu().numpy(), r.cpu().numpy())
         B.mgi_plan_set_node_config(plan.handle, i, 0)
+
+
+@pytest.mark.parametrize("kind,src,dtype", [("dw3", 0, 0), ("dw3", 2, 1), ("dw5", 2, 0), ("pw", 0, 0), ("conv", 0, 0)])
+def test_tensors_not_written(kind, src, dtype):
+    """What the workspace holds after a run tells which tensors were stored: with
+    the input read in place and the output written by the GEMM, only the one
+    between them; with an input off 16 bytes its converted form too; with an
+    output over the input also the GEMM's sliced result."""
+    import torch
+    from paper_1907_01989_amd import engine, _binding as B
+    n, h, w, c, cout = 2, 12, 11, 64, 48
+    g = NetBuilder(seed=6)
+    t = x = g.input(n, h, w, c, 0.5, 1.0, dtype=src)
+    if kind in ("dw3", "dw5"):
+        t = g.dw(t, int(kind[2]))
+    elif kind == "conv":
+        t = g.conv(t, c, 3)
+    else:
+        t = g.conv(t, c, 1)
+    g.mark_output(g.conv(t, cout, 1))
+    plan = engine.Plan(g.graph("stored"), planner=B.PLANNER_NAIVE, dtype=dtype)
+    x = plan.input_tensors()[0]
+    elems = n * h * w * np.array([c // 8, c // 8, cout // 8])        # converted input, middle, sliced output
+    both = torch.empty(x.numel() * 2 + 4096, dtype=x.dtype, device=x.device)
+
+    def stored(xo, yo):
+        plan.ws.fill_(0xa5)                     # a small negative number in fp16 and bf16: no ReLU6 output
+        plan.run([xo], [yo])
+        torch.cuda.synchronize()
+        base = plan._ws_ptr - plan.ws.data_ptr()
+        words = plan.ws[base:base + plan.workspace_bytes // 16 * 16].view(-1, 16)
+        return int((words != 0xa5).any(1).sum())
+
+    want = plan.alloc_outputs()[0]
+    log(f"[case] stored tensors {kind} src {src} store {dtype}")
+    assert stored(x, want) == elems[1]
+    off = torch.empty(x.numel() + 1, dtype=x.dtype, device=x.device)[1:].view(x.shape)
+    off.copy_(x)
+    y = torch.empty_like(want)
+    assert stored(off, y) == elems[0] + elems[1]
+    assert torch.equal(y, want)
+    xo = both[:x.numel()].view(x.shape)
+    xo.copy_(x)
+    yo = both.view(torch.float32)[:want.numel()].view(want.shape)
+    assert stored(xo, yo) == elems.sum()
+    assert torch.equal(yo, want)
+    plan.close()
