@@ -345,8 +345,8 @@ mgi_status mgi_plan_read_node_raw(mgi_plan *p, int i, void *dev_dst, size_t *byt
  * `reps` whole runs of the plan, queued back to back (plus one warm-up run;
  * only the node's kernels are timestamped, so it meets its input as in a
  * run; a candidate that alone keeps a graph input from being read in place
- * counts the conversion kernel too), and keeps the one with the lowest
- * median time (a candidate listed
+ * counts the conversion kernel too), and keeps the one whose times have the
+ * lowest lower quartile (a candidate listed
  * later replaces an earlier one only when more than 2% faster; fused forms
  * are listed before split ones).  All candidates produce bit-identical
  * results.  Synchronises `stream` once per candidate; releases a captured
