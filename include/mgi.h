@@ -115,10 +115,12 @@ typedef struct {
                             output feeds nothing else; the pointwise output then never
                             reaches memory (Sec. 3.2's fusion extended to the pointwise ->
                             depthwise pair).  0: never; 1 (default): the fused kernel is the
-                            default configuration when it gets at least 128 workgroups (tiles
-                            x channel tiles; below that the separate kernels are), the other
-                            one an autotune candidate; 2: the fused kernel is the default
-                            whenever the shapes allow.  Needs fuse = 1. */
+                            default configuration when one of its tilings gets at least 128
+                            workgroups (bands of 16 channels, which repeat the most work, do
+                            not count; below that the separate kernels are), the one with the
+                            lowest estimated time first; the other forms are autotune
+                            candidates; 2: the fused kernel is the default whenever the
+                            shapes allow.  Needs fuse = 1. */
     int fuse_stemdw;     /* the same for the stem (a convolution over the graph input with
                             kh*kw*c <= 32 and at most 64 output channels) and a 3x3 depthwise
                             convolution at stride 1 that alone reads its output: 0, 1
@@ -133,9 +135,10 @@ typedef struct {
                             last runs their softmax, bit-identical to the two operators.  Its
                             arrival counters live in the workspace past the arena, zeroed by
                             mgi_plan_bind and left at zero by every run.  The fused kernel is
-                            the default configuration for at most 16 rows (the two kernels
-                            above that), the other one an autotune candidate.  0 or 1
-                            (default).  Needs fuse = 1. */
+                            the default configuration for at most 16 rows, and for rows of at
+                            most 384 classes in at most 96 workgroups (the two kernels above
+                            that), the other one an autotune candidate.  0 or 1 (default).
+                            Needs fuse = 1. */
     int fuse_irb;        /* run a 1x1 projection convolution (stride 1, at most 320 output
                             channels, optional residual add) inside a fused pointwise ->
                             depthwise node (fuse_pwdw) whose output only it reads: MobileNet-v2's

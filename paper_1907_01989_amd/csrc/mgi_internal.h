@@ -104,16 +104,17 @@ enum class NodeKind {
 };
 
 // Tile shape of the MFMA GEMM (pointwise, implicit-GEMM convolution, FC).
-// pipe = true selects the pipelined pointwise kernel with bm x bn tiles;
-// slab = true the weight-slab pointwise kernel with (4 * wm) x bn tiles and
-// pf K steps of activation prefetch; otherwise the LDS-staged kernel with
-// bm x bn tiles.
+// pipe = true selects the pipelined ring kernel (pointwise or windowed) with
+// bm x bn tiles; slab = true the weight-slab pointwise kernel with (4 * wm) x
+// bn tiles and pf K steps of activation prefetch; otherwise the LDS-staged
+// kernel with bm x bn tiles.
 struct GemmTile {
     int bm = 64, bn = 64;
     bool pipe = false;
     bool slab = false;
     int wm = 32, pf = 1;
-    int ks = 4;             // pipe: K slices per ring stage (4, or 8 for 64 x 64 tiles)
+    int ks = 4;             // pipe: K slices per ring stage (4, or 8 for pointwise 64 x 64 and
+                            // windowed 64 x 32 and 128 x 32 tiles)
 };
 
 struct Node {
@@ -167,9 +168,9 @@ struct Node {
     bool fused_default = true;
     int pwdw_first = 0;         // PwDw / StemDw: the fused kernel's configuration that is listed first
     bool irb_default = false;   // Irb: the block kernel is the default configuration
-    int pwdw_cfg = 0;       // PwDw / StemDw: configuration of the fused kernel (pwdw_configs,
-                            // stemdw_configs)
-    kern::PwDwGeom pwdw_geo{};
+    int pwdw_cfg = 0;       // StemDw, Irb (mode 0): configuration of the fused kernel
+                            // (stemdw_configs, irb_configs)
+    kern::PwDwGeom pwdw_geo{};   // PwDw, Irb (mode 1): geometry of the fused pair's kernel
     size_t cnt_off = 0;     // FcSoftmax: its row-tile arrival counters in the workspace's
                             // state region
     // Irb (a PwDw node that also runs the pointwise projection reading its
@@ -184,7 +185,7 @@ struct Node {
     int scratch2 = -1;
     GemmTile pj_tile;
     int mode = 0;           // Irb: 0 the block kernel (pwdw_cfg: its configuration), 1 the fused
-                            // pointwise -> depthwise kernel (pwdw_cfg) then the projection GEMM,
+                            // pointwise -> depthwise kernel (pwdw_geo) then the projection GEMM,
                             // 2 three kernels (expansion GEMM `tile`, depthwise, projection GEMM)
     struct Config {
         GemmTile tile;

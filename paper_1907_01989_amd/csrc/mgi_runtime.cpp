@@ -843,11 +843,12 @@ extern "C" mgi_status mgi_plan_replay(mgi_plan *p, void *stream) {
 // measurement (Sec. 4.2): every node with more than one candidate
 // configuration is launched reps + 1 times per candidate on the plan's own
 // buffers (after one full run has filled them), each launch timestamped on the
-// device; the one with the lowest lower quartile over the timed launches (the first
-// launch being a warm-up; the conversion of an input that this candidate alone
-// keeps from being read in place counts with it) is kept, a later candidate replacing an earlier one
-// only when more than 2% faster.  Candidates compute identical results, so tuning changes
-// speed only.  A captured graph holds the old configurations and is released.
+// device; the one with the lowest lower quartile over the timed launches (the
+// first launch being a warm-up; the conversion of an input that this candidate
+// alone keeps from being read in place counts with it) is kept, a later
+// candidate replacing an earlier one only when more than 2% faster.  Candidates
+// compute identical results, so tuning changes speed only.  A captured graph
+// holds the old configurations and is released.
 extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inputs,
                                         void *const *dev_outputs, void *stream, int reps) {
     MGI_ABI_TRY
