@@ -797,7 +797,7 @@ static hipError_t launch_conv_e(const GemmParams &p, int bm, int bn, int ks, hip
 
 hipError_t launch_gemm_conv(const GemmParams &p, int bm, int bn, int ks, hipStream_t st) {
     if (p.M <= 0) return hipSuccess;
-    if (!p.taps || !p.zero || p.sin < 1 || p.kh < 1 || p.kw < 1 || p.ksp % 8 != 0 || p.ksl != p.kh * p.kw * p.sin ||
+    if (!p.taps || !p.zero || p.sin < 1 || p.kh < 1 || p.kw < 1 || p.ksp % ks != 0 || p.ksl != p.kh * p.kw * p.sin ||
         !conv_pipe_ok(conv_geom(p), p.ksp))
         return hipErrorInvalidValue;
     return p.bf16 ? launch_conv_e<BF16>(p, bm, bn, ks, st) : launch_conv_e<F16>(p, bm, bn, ks, st);

@@ -804,6 +804,8 @@ void pick_pipe_tile(GemmTile &t, size_t M, int npad) {
 //    16-channel weight slab with the 8-step prefetch (784 x 464 -> 160 4.4 us
 //    against 7.2 for the pipelined 64 x 64 tile, 49 x 960 -> 160 4.6 / 6.5,
 //    576 x 256 -> 256 4.0 / 6.0);
+//    (not where exact_k_tail: the slab kernel has no such loader; 784 x 872 ->
+//    24 8.6 us by the ring's window loader against 5.5, the staged kernel 15.6);
 //  - K >= 64 and at least 64 channels: the pipelined kernel;
 //  - else, K above 512: the pipelined 64 x 64 tile, half of it empty
 //    (10192 x 864 -> 24 7.5 us against 9.1 for a 32-channel slab and 16.4 for
@@ -813,7 +815,8 @@ void pick_pipe_tile(GemmTile &t, size_t M, int npad) {
 //    fill the compute units; two K steps of prefetch when there are two.
 GemmTile pick_pw_tile(size_t M, int npad, int ksl, int ksp) {
     GemmTile t;
-    if (ksp >= 32 && (M + 63) / 64 * (size_t)(npad / 16) < 256 && kern::gemm_xs_lds_bytes(ksp, 16, 16) <= 160 * 1024) {
+    if (ksp >= 32 && !exact_k_tail(npad, ksl, ksp) && (M + 63) / 64 * (size_t)(npad / 16) < 256 &&
+        kern::gemm_xs_lds_bytes(ksp, 16, 16) <= 160 * 1024) {
         t.slab = true;
         t.wm = 16;
         t.bn = 16;
@@ -1173,7 +1176,9 @@ mgi_status Lowering::lower_conv(const Group &G, const GOp &op, const Shape &out_
     if (nd.kind == NodeKind::Gemm && nd.taps && nd.ksp % 8 == 0 && kern::conv_pipe_ok(conv_geom(d, x, out_shape), nd.ksp)) {
         nd.tile = pick_conv_tile(out_shape.pixels(), nd.nb16 * 16);
     } else if (nd.kind == NodeKind::Gemm && !nd.taps) {
-        nd.tile = pick_pw_tile(out_shape.pixels(), nd.nb16 * 16, nd.ksl, nd.ksp);
+        const GemmTile t = pick_pw_tile(out_shape.pixels(), nd.nb16 * 16, nd.ksl, nd.ksp);
+        if (!exact_k_tail(nd.nb16 * 16, nd.ksl, nd.ksp) || kern::conv_pipe_ok(conv_geom(d, x, out_shape), nd.ksp))
+            nd.tile = t;
     }
     if (G.residual_tensor >= 0) {
         int rb = need_c8(G.residual_tensor);

@@ -265,11 +265,23 @@ inline kern::ConvGeom conv_geom(const mgi_conv_desc &d, const Shape &x, const Sh
     return {x.h, x.w, y.h, y.w, d.kh, d.kw, d.stride_h, d.stride_w, d.dil_h, d.dil_w, d.pad_t, d.pad_l};
 }
 
+// Narrow pointwise products with K above 768 and not whole steps of 32: their
+// default tile runs through the ring's window loader, as a 1x1 window.  It reads
+// the zero element for K slices past the end; the pointwise loaders read the last
+// real slice there, against zero weights, which turns an infinity in it into a
+// NaN.  (Zeros in the pointwise loader's last stage slow all its loops: 28 x 28 x
+// 256 chains 98.6 us, 106 by address, 158 by value.)
+inline bool exact_k_tail(int npad, int ksl, int ksp) { return npad < 64 && ksp > 96 && ksl != ksp; }
+inline bool window_1x1(const Node &nd) {
+    return !nd.taps && nd.tile.pipe && nd.tile.bm == 64 && nd.tile.bn == 64 && nd.tile.ks == 4 &&
+           exact_k_tail(nd.nb16 * 16, nd.ksl, nd.ksp);
+}
+
 // Whether node nd, in its configuration, can read an input in place (a window
 // GEMM's ring walks whole taps per stage; every other kernel of the kinds
 // absorb_ingests lists can).
 inline bool reads_in_place(const mgi_plan &p, const Node &nd) {
-    if (nd.kind != NodeKind::Gemm || !nd.taps || !nd.tile.pipe) return true;
+    if (nd.kind != NodeKind::Gemm || !nd.tile.pipe || !(nd.taps || window_1x1(nd))) return true;
     const Shape &x = p.bufs[nd.in[0]].shape;
     return kern::conv_nhwc_ok(conv_geom(nd.conv, x, p.bufs[nd.out].shape), (x.c + 7) / 8, nd.tile.ks);
 }

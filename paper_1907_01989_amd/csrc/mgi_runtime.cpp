@@ -510,7 +510,8 @@ hipError_t launch_node(const mgi_plan &p, const Node &nd, const Bases &B, hipStr
             q.taps = nd.taps;
             q.zero = (const h8 *)(wbase + p.zero_off);
             if (nd.kind == NodeKind::FC) return launch_fc(q, nd.tile.wm, nd.tile.pf, st);
-            if (nd.tile.pipe && nd.taps) return launch_gemm_conv(q, nd.tile.bm, nd.tile.bn, nd.tile.ks, st);
+            if (window_1x1(nd) && conv_pipe_ok(conv_geom(nd.conv, ib.shape, os), nd.ksp)) q.taps = 1;
+            if (nd.tile.pipe && q.taps) return launch_gemm_conv(q, nd.tile.bm, nd.tile.bn, nd.tile.ks, st);
             if (nd.tile.pipe && nd.tile.ks == 8) return launch_gemm_pipe_k8(q, false, st);
             if (nd.tile.pipe) return launch_gemm_pipe(q, nd.tile.bm, nd.tile.bn, st);
             if (nd.tile.slab) return launch_gemm_xs(q, nd.tile.wm, nd.tile.bn, nd.tile.pf, false, st);
@@ -863,7 +864,7 @@ extern "C" mgi_status mgi_plan_autotune(mgi_plan *p, const void *const *dev_inpu
     // window GEMM's runs have pairs for the conversions of its operands too
     size_t pairs = 1;
     for (const Node &nd : p->nodes)
-        if (nd.kind == NodeKind::Gemm && nd.taps) pairs = 3;
+        if (nd.kind == NodeKind::Gemm && (nd.taps || exact_k_tail(nd.nb16 * 16, nd.ksl, nd.ksp))) pairs = 3;
     std::vector<hipEvent_t> evs(2 * pairs * (size_t)(reps + 1), nullptr);
     hipError_t e = hipSuccess;
     for (size_t k = 0; k < evs.size() && e == hipSuccess; ++k) e = hipEventCreate(&evs[k]);

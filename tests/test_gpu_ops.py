@@ -480,3 +480,41 @@ def test_depthwise_every_row_count(n, h, w, c, s, d, dtype):
     check_isolated("dw", outs[0], ref.reshape(outs[0].shape), rtol=ISO_RTOL_BF16 if dtype else ISO_RTOL)
     for o in outs[1:]:
         np.testing.assert_array_equal(o, outs[0])
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [(1, 7, 7, 776, 24), (3, 33, 31, 792, 24), (16, 28, 28, 872, 40), (2, 9, 9, 779, 16),
+                                            (1, 1, 1, 1000, 48)])
+@pytest.mark.parametrize("src,dtype", [(workloads.DTYPE_FP16, 0), (workloads.DTYPE_FP32, 0), (workloads.DTYPE_FP16, 1)])
+def test_infinity_beside_the_k_tail(n, h, w, cin, cout, src, dtype):
+    """Narrow pointwise products with K above 768 and not whole steps of 32: an
+    infinity in the last real K slice meets that slice's weights only, not the
+    zero weights of the padding behind it (the default configuration; finite
+    inputs in every one, bit for bit)."""
+    import torch
+    from paper_1907_01989_amd import engine, _binding as B
+    g = NetBuilder(seed=cin)
+    t = g.conv(g.input(n, h, w, cin, 0.0, 1.0, dtype=src), cout, 1, act=ACT_NONE)
+    g.mark_output(t)
+    desc = g.graph("tail")
+    plan = engine.Plan(desc, dtype=dtype)
+    x = plan.input_tensors()[0]
+    node = [i for i, k in enumerate(plan.nodes()) if k["kind"] == "pw_gemm"][0]
+    first = None
+    for c in range(plan.node_configs()[node][1]):
+        B.mgi_plan_set_node_config(plan.handle, node, c)
+        log(f"[case] tail {n}x{h}x{w} {cin}->{cout} input {src} store {dtype} {plan.node_configs()[node][2]}")
+        y = plan.run([x])[0].cpu()
+        if first is None:
+            first = y
+            store = torch.bfloat16 if dtype else torch.float16
+            wt = torch.from_numpy(desc["ops"][t]["w"].reshape(cout, cin)).to(store).float()
+            ref = x.cpu().to(store).double().reshape(-1, cin) @ wt.double().t() + torch.from_numpy(desc["ops"][t]["b"]).double()
+            ok, msg = check_layer("tail", y.numpy().reshape(ref.shape), ref.numpy(), ISO_RTOL_BF16 if dtype else ISO_RTOL)
+            assert ok, msg
+        assert torch.equal(y, first), plan.node_configs()[node][2]
+    B.mgi_plan_set_node_config(plan.handle, node, 0)
+    x[n - 1, h - 1, w - 1, cin - 1] = float("inf")
+    y = plan.run([x])[0].cpu().reshape(-1, cout)
+    assert torch.equal(y[-1], wt[:, cin - 1] * float("inf"))
+    assert torch.equal(y[:-1], first.reshape(-1, cout)[:-1])
+    plan.close()
