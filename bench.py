@@ -238,7 +238,7 @@ def kernel_sources_hash():
     while the kernels it was measured on are unchanged."""
     import hashlib
     h = hashlib.sha1()
-    for f in ("gemm.hip", "ops.hip", "dwpw.hip", "pwdw.hip", "stemdw.hip", "irb.hip", "device.h", "kernels.h"):
+    for f in ("gemm.hip", "ops.hip", "dwpw.hip", "pwdw.hip", "stemdw.hip", "irb.hip", "device.h", "rowunit.h", "kernels.h"):
         with open(os.path.join(ROOT, "paper_1907_01989_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
