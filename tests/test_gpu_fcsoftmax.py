@@ -77,7 +77,8 @@ def test_fused_fc_softmax(n, K, classes):
 
 @pytest.mark.parametrize("n,classes,first", [
     (1, 1, "fc"), (16, 64, "fc"), (17, 128, "fc"), (33, 129, "fc"), (64, 384, "fc"), (65, 384, "split"),
-    (19, 385, "split"), (21, 1024, "split"), (15, 1025, "fc"), (256, 96, "fc"), (257, 96, "split")])
+    (19, 385, "split"), (21, 1024, "split"), (15, 1025, "fc"), (256, 96, "fc"), (257, 96, "split"),
+    (5, 1000, "fc"), (7, 300, "fc"), (8, 100, "fc"), (4, 1000, "fc"), (9, 600, "fc")])
 def test_rows_in_registers(n, classes, first):
     # every register count of the row routine at its edges, a tile's rows
     # finished together (full, ragged and single), and which form comes first
