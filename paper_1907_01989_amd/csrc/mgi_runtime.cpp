@@ -36,8 +36,8 @@ struct Bases {
 };
 
 // Whether no output buffer of a run shares bytes with an input buffer (a
-// caller may run in place: its inputs are then read before any output is
-// written, as when every output has an export kernel at the end).
+// caller may run in place: its inputs are then converted before their first
+// reader and its outputs exported behind their producers).
 bool io_disjoint(const mgi_plan &p, const void *const *ins, void *const *outs) {
     for (size_t i = 0; i < p.input_bufs.size(); ++i)
         for (size_t o = 0; o < p.output_bufs.size(); ++o) {
