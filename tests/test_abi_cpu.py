@@ -594,6 +594,35 @@ def test_concat_views_need_no_more_memory_than_the_copy(planner, widths, views):
     plan.close()
 
 
+@pytest.mark.parametrize("planner", [B.PLANNER_GREEDY, B.PLANNER_MCFP])
+@pytest.mark.parametrize("wide", [(), (0,), (3,), (6,), (0, 2, 5), (0, 1, 2, 3, 4, 5, 6)])
+def test_concat_views_beside_concats_that_keep_the_copy(planner, wide):
+    """Seven concatenations, some of which would make the arena larger: it never
+    is larger than with copies."""
+    g = workloads.NetBuilder(seed=0)
+    t = g.input(1, 8, 8, 40, 0.0, 1.0)
+    for k in range(7):
+        a = g.conv(t, 8, 1)
+        c, b = (512, 256) if k in wide else (16, 16)
+        t = g.conv(g.concat([a, g.conv(g.conv(g.conv(t, c, 1), c, 1), b, 1)]), 24, 1)
+    g.mark_output(t)
+    desc = g.graph("concats")
+    plan = engine.Plan(desc, bind=False, planner=planner)
+    assert len(plan.nodes()) == len(desc["ops"]) + 1           # ingest, the layers in order, export
+    last = [0] * len(desc["ops"])
+    for k, op in enumerate(desc["ops"]):
+        for s in op.get("ins", [op.get("in")]):
+            if s is not None:
+                last[s] = k
+    last[-1] = len(desc["ops"])
+    sizes = [(n["shape"][3] + 7) // 8 * 64 * 16 for n in plan.nodes()[:-1]]
+    _, copied = B.mgi_planner_assign(planner, sizes, list(range(len(sizes))), last)
+    naive, planned, _ = plan.memory_report()
+    assert naive == sum(sizes)
+    assert planned <= sum(copied)
+    plan.close()
+
+
 @pytest.mark.parametrize("n,hw,cin,cout,k,count", [(4, 33, 256, 256, 3, 5), (1, 7, 32, 24, 3, 3), (2, 14, 512, 512, 1, 9)])
 def test_gemm_configuration_numbers_stay_valid(n, hw, cin, cout, k, count):
     """A stored tuning is a list of configuration numbers: every number that a
